@@ -334,8 +334,9 @@ dte::ExtractParams extract_params(const float* p, const float* m, const float* v
         // one binary32 step below and above the binary64 reciprocal: a
         // bracket of 1/decay whatever the binary64 rounding did
         const float r = (float)(1.0 / (double)sc.s.decay);
-        a.rd_lo = std::nextafter(r, 0.0f);
-        a.rd_hi = std::nextafter(r, INFINITY);
+        const bool grows = sc.s.decay < 1.0f;     // 1/decay > 1
+        a.rd = std::nextafter(r, grows ? INFINITY : 0.0f);
+        a.far = grows ? 0xFFFFFFFFu : 0u;
     }
     a.literal = sc.s.order == DTE_ORDER_LITERAL;
     a.lr = sc.s.lr;
@@ -374,8 +375,12 @@ constexpr int64_t kNoallocBytes = (int64_t)64 << 20;
 OrderedWorkspace ordered_layout(int64_t capacity)
 {
     OrderedWorkspace w;
-    // every flush but a wave's last holds exactly kWaveStage entries
-    w.max_runs = capacity / dte::kWaveStage + dte::kMaxOrderedWaves + 1;
+    // every flush but a wave's last holds exactly kWaveStage entries; at most
+    // kMaxWaves waves run (the first bound keeps the size, and so the largest
+    // capacity of the call without a workspace argument, what it was with
+    // flushes of 1536 entries)
+    w.max_runs = std::max(capacity / 1536 + dte::kMaxOrderedWaves + 1,
+                          capacity / dte::kWaveStage + dte::kMaxWaves + 1);
     w.ridx = 0;
     w.rval = align256(w.ridx + capacity * (int64_t)sizeof(int64_t));
     w.idx = align256(w.rval + capacity * (int64_t)sizeof(uint16_t));
@@ -437,16 +442,16 @@ dte_status extract_ordered(const float* p, const float* m, const float* v, int64
     a.region_idx = reinterpret_cast<int64_t*>(base + w.ridx);
     a.region_val = reinterpret_cast<uint16_t*>(base + w.rval);
     a.region_count = reinterpret_cast<int64_t*>(base + w.region_count);
-    a.region_size = capacity / dte::extract_waves(a, cus);
-    int32_t waves = 0;
-    if (dte::launch_extract(a, cus, s, &waves) != hipSuccess) return DTE_ERR_HIP;
+    const int64_t waves = dte::extract_waves(n, cus);
+    a.region_size = capacity / waves;
+    if (dte::launch_extract(a, cus, s) != hipSuccess) return DTE_ERR_HIP;
     dte::OrderParams o;
     o.runs = a.runs;
     o.run_cursor = a.run_cursor;
     o.max_runs = w.max_runs;
     o.wave_count = a.wave_count;
     o.wave_base = reinterpret_cast<int64_t*>(base + w.wave_base);
-    o.waves = waves;
+    o.waves = (int32_t)waves;
     o.src_idx = a.out_idx;
     o.src_val = a.out_val;
     o.src_capacity = capacity;

@@ -64,7 +64,8 @@ struct ExtractParams {
     int64_t n;            // elements of this call
     int64_t index_base;   // flat trainer offset of element 0
     float lrb1, rbc2, eps, decay;
-    float rd_lo, rd_hi;   // binary32 bracket of 1/decay: rd_lo <= 1/decay <= rd_hi
+    float rd;             // bracket of 1/decay away from 1 (proven_unchanged), and
+    uint32_t far;         // which magnitude of p and hi it scales
     int32_t literal;      // order: 0 folded, 1 literal
     float lr, bc1, bc2;   // literal order
     int32_t lit_filter;   // literal order: the "unchanged" proof may be used
@@ -88,7 +89,6 @@ struct ExtractParams {
     uint16_t* region_val;
     int64_t* region_count;
     int64_t region_size;      // entries per wave region
-    int32_t wave0;        // global number of this launch's first wave
     // routing mode (route != 0): each flush sends its entries through the
     // plan into the receiver buckets (out, counts added to rank_count)
     // instead of writing (out_idx, out_val); the cursor still counts them
@@ -98,19 +98,19 @@ struct ExtractParams {
     int64_t* rank_count;
 };
 
-// Largest number of waves one extract call launches in ordered mode.
+// Waves that the ordered workspace's tables have room for, and the most that
+// one extract call launches.
 constexpr int kMaxOrderedWaves = 16384;
+constexpr int kMaxWaves = 4096;
 // Entries a wave stages before it flushes them: every flush but a wave's
 // last holds exactly this many (the ordered workspace is sized with it).
-constexpr int kWaveStage = 1536;
+constexpr int kWaveStage = 1408;
 
-// Launches the extract kernels; *waves receives the number of waves
-// launched (the global wave numbers are 0 .. *waves - 1).
-hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream,
-                          int32_t* waves = nullptr);
+// Launches the extract kernel over extract_waves(a.n, cus) waves.
+hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream);
 
-// The number of waves launch_extract(a, cus, ...) launches.
-int64_t extract_waves(const ExtractParams& a, int cus);
+// The number of waves launch_extract launches for n elements.
+int64_t extract_waves(int64_t n, int cus);
 
 // Ordered mode, after launch_extract: wave_base[g] = *cursor + entries of
 // waves < g; copies every wave's region part to (out_idx, out_val) at

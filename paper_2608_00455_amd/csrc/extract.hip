@@ -6,24 +6,22 @@
 // Design (HBM-bound: 12 bytes read per element, ~10 bytes written per
 // changed element):
 //  - persistent grid of one block of 12 waves per CU (three per SIMD, the
-//    VGPR limit; the block holds the CU's whole LDS) over the full tiles,
-//    three blocks of 4 waves per CU over ragged ones; each wave owns one
-//    contiguous range of 2048-element tiles, ranges ascending with the
-//    global wave number, so every wave's entries leave in ascending order;
-//    in the unordered call the static ranges leave out the last 1/16 of
-//    the full tiles, which blocks then take four tiles per wave at a time
-//    from a counter (the CUs do not stream at one rate, and a static split
-//    leaves the fast ones idle at the end);
-//    a wave loads eight float4 of p, m and v per lane, i.e. 24 16-byte
-//    non-temporal loads in flight per lane, which is what keeps the HBM
-//    queues full at this occupancy;
+//    VGPR limit; the block holds the CU's whole LDS); each wave owns one
+//    contiguous range of 256-element slots (one float4 per lane), ranges
+//    ascending with the global wave number, so every wave's entries leave in
+//    ascending order; in the unordered call the static ranges leave out the
+//    last 1/16 of the slots, which blocks then take eight slots per wave at a
+//    time from a counter (the CUs do not stream at one rate, and a static
+//    split leaves the fast ones idle at the end);
+//    a wave keeps two slots of p, m and v in flight, reloading each slot's
+//    registers as soon as it is tested;
 //  - proof of "unchanged" before exact arithmetic: with DECAY == 1 the
 //    reconstruction is ph = RN(p + u), where u has the sign of m and
 //    |u| <= B; B comes from the hardware square root and reciprocal (about
 //    1 ulp each), inflated by 2^-16, plus 2^-126; RN and BF16 rounding are
 //    monotone, so if RN(p + sign(m) B) has the BF16 pattern of p, so has ph.
-//    (DECAY != 1: the same interval is pushed through the division with
-//    bracketing reciprocals of DECAY.)  Lanes without that proof
+//    (DECAY != 1: the same interval is pushed through the division with a
+//    bracketing reciprocal of DECAY.)  Lanes without that proof
 //    (candidates, about as many as the changed elements) queue
 //    (p, m, v, position) in LDS; a wave evaluates 64 queued candidates at a
 //    time with the correctly rounded inverse.  The result is bit-identical
@@ -33,16 +31,16 @@
 //    elements) is four ballots; an element's position among the slot's
 //    selected elements is the sum of mbcnt over the four ballots (lanes
 //    before it) plus its own selected predecessors in the lane, so
-//    candidates are queued, and changed entries (packed 32-bit position +
+//    candidates are queued, and changed entries (32-bit position +
 //    BF16 value) staged in LDS, in ascending element order: every wave's
 //    output is ascending.  In the unordered call the waves of a block meet
-//    every four tiles and, once they hold enough entries, reserve output
+//    every one to four passes over the ring and, once they hold enough entries, reserve output
 //    space for all of them with one atomicAdd on the 64-bit cursor
 //    (block_round below); each wave writes its run after those of the waves
 //    before it, coalesced.  A wave whose staging area (kWaveStage entries)
 //    fills between two meetings flushes exactly kWaveStage entries on its
 //    own with one atomicAdd;
-//  - ordered mode: the waves of a block still meet every four tiles (a
+//  - ordered mode: the waves of a block still meet every four passes (a
 //    barrier alone), which keeps them in step; each wave writes its
 //    flushes to a region of the workspace of its own (no atomics) and,
 //    once that is full, to a shared
@@ -61,22 +59,32 @@
 namespace dte {
 namespace {
 
-// Waves per block: 12 (one block per CU) for full tiles; the ragged-tile
-// kernels need more VGPRs than 12 waves per CU leave without spilling, and
-// run as 4-wave blocks, three per CU.  Either way 3 waves per SIMD.
-template <bool kFull> constexpr int kWavesOf = kFull ? 12 : 4;
-constexpr int kWavesPerCU = 12;
-constexpr int kVec = 8;                       // float4 per lane per array per tile
-constexpr int kSlots = 4 * kVec;              // elements per lane per tile
-constexpr int kWaveTile = 64 * kSlots;        // 2048 elements per wave tile
-constexpr int kQueue = 256;                   // queued candidates per wave (16 bytes each)
-// a float4 slot selects up to 4 x 64 elements at once: they must fit an
-// empty candidate queue, and the part left after one flush of the staging
-// area must fit the emptied area
-static_assert(kQueue >= 4 * 64, "a slot's candidates must fit the queue");
-static_assert(kWaveStage >= 4 * 64, "a slot's changed entries must fit after one flush");
+constexpr int kWaves = 12;                    // waves per block, one block per CU
+// float4 slots in flight per lane and array.  Measured with 8 / 4 / 3 / 2 (386
+// M elements, us): lr 1e-6 698 / 691 / 689 / 678, 1e-5 767 / 759 / 762 /
+// 757, 1e-4 906 / 894 / 890 / 883; 44 M elements in 13 odd ranges 330 / 299
+// / 296 / 285: the code of a pass grows with it, and 12 waves keep the HBM
+// queues full with two.
+constexpr int kVec = 2;
+constexpr int kSlot = 256;                    // elements of one slot of a wave (a float4 per lane)
+constexpr int kQueue = 320;                   // queued candidates per wave (16 bytes each)
+constexpr int kDrain = 64;                    // queued candidates that are drained after a slot
+// Slots per wave before another block is added: every block ends with one
+// atomicAdd on the caller's cursor, and 256 of these in a row take about
+// 10 us.  2 M elements (zeroing the cursor and the call, between events):
+// 33.8 us with 1 slot per wave (256 blocks), 34.1 with 2, 28.8 with 4
+// (163 blocks), 29.3 with 8; 1e5 elements 22.8 / 23.0 / 23.8 / 25.0.
+constexpr int kMinSlots = 4;
+// what is left undrained (fewer than kDrain) and a slot's 4 x 64 elements
+// must fit the queue; the part of a slot left after one flush of the
+// staging area must fit the emptied area
+static_assert(kQueue >= kDrain - 1 + kSlot, "a slot's candidates must fit the queue");
+static_assert(kWaveStage >= kSlot, "a slot's changed entries must fit after one flush");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));   // element-aligned
+typedef const __attribute__((address_space(1))) f32x4_any* global_f32x4;
+typedef const __attribute__((address_space(1))) float* global_f32;
 
 // Adaptive step term u = (lrb1*m) / (sqrt(v*rbc2) + eps): four binary32
 // operations, each rounded once (sqrt and divide correctly rounded).
@@ -146,6 +154,17 @@ __device__ __forceinline__ f32x4 load4(const float* base, int64_t e, int64_t n)
 // finite (other elements take the exact path); v*rbc2 is clamped to the
 // largest finite value so that it cannot overflow where v/bc2 does not
 // (a NaN stays NaN).
+//
+// DECAY != 1: theta_hat = RN(w / DECAY) for some w between p and hi, so it
+// lies between the smallest and the largest of p, hi, p / DECAY and
+// hi / DECAY.  Where p and hi have one sign (else hi's pattern differs) the
+// two outer ones of these are, for DECAY < 1, the smaller magnitude of p
+// and hi themselves and the larger magnitude times an upper bracket of
+// 1 / DECAY; for DECAY > 1 the larger magnitude itself and the smaller
+// times a lower bracket.  p has its own pattern, so testing hi and that
+// product tests both ends.  `rd` is the bracket; the median of (p, hi,
+// far) as unsigned patterns is the larger magnitude for far = 2^32 - 1 and
+// the smaller for far = 0.
 template <bool kDecayOne, bool kLit>
 __device__ __forceinline__ bool proven_unchanged(float p, float m, float v, const ExtractParams& a)
 {
@@ -161,14 +180,12 @@ __device__ __forceinline__ bool proven_unchanged(float p, float m, float v, cons
     const uint32_t rp = up + 0x7FFFu + ((up >> 16) & 1u);
     const uint32_t rh = uh + 0x7FFFu + ((uh >> 16) & 1u);
     if (kDecayOne) return in_range & ((rp ^ rh) < 0x10000u);
-    const float x0 = p * a.rd_lo, x1 = p * a.rd_hi, x2 = hi * a.rd_lo, x3 = hi * a.rd_hi;
-    const float mn = __builtin_fminf(__builtin_fminf(x0, x1), __builtin_fminf(x2, x3));
-    const float mx = __builtin_fmaxf(__builtin_fmaxf(x0, x1), __builtin_fmaxf(x2, x3));
-    const uint32_t un = __float_as_uint(mn), ux = __float_as_uint(mx);
-    const uint32_t rn = un + 0x7FFFu + ((un >> 16) & 1u);
-    const uint32_t rx = ux + 0x7FFFu + ((ux >> 16) & 1u);
-    return in_range & ((rp ^ rn) < 0x10000u) & ((rp ^ rx) < 0x10000u) & (mn == mn) & (mx == mx) &
-           (hi == hi);
+    const uint32_t small = up < uh ? up : uh, large = up < uh ? uh : up;
+    const uint32_t capped = large < a.far ? large : a.far;
+    const uint32_t outer = small > capped ? small : capped;      // median
+    const uint32_t uy = __float_as_uint(__uint_as_float(outer) * a.rd);
+    const uint32_t ry = uy + 0x7FFFu + ((uy >> 16) & 1u);
+    return in_range & (((rp ^ rh) | (rp ^ ry)) < 0x10000u);
 }
 
 // Exact inverse and change test of one element (sec. 4.1 / 4.2.1).
@@ -181,37 +198,36 @@ __device__ __forceinline__ float exact_prev(float p, float m, float v, const Ext
     return kDecayOne ? num : num / a.decay;
 }
 
-constexpr int kTileBits = __builtin_ctz(kWaveTile);
-constexpr int64_t kDenseRatio = 64;             // see flush_wave
-static_assert((1 << kTileBits) == kWaveTile, "wave tile must be a power of two");
+constexpr int64_t kDenseRatio = 64;             // see write_staged
 
-// Dynamic tail of the unordered call over full tiles: when the waves have
-// at least kTailDiv tiles each, the last total / kTailDiv tiles (at most
-// 2^20, so that a tile's offset from the tail's start fits a staging key)
-// go to blocks four tiles per wave (one flush round) per grab.  A grab adds 2^kGrabShift to the caller's cursor, whose bits below
-// kGrabShift count the entries (a delta never reaches 2^36 entries): the
-// old value's high bits number the chunk, every reservation masks them off,
-// and clear_grabs_kernel clears them once the kernel is done.
+// Dynamic tail of the unordered call: when the waves have at least
+// kTailSlots slots each, the last total / kTailDiv slots (at most 2^23, so
+// that an element's offset from the tail's start fits a staging key) go to
+// blocks kRound passes per wave per grab.  A grab adds
+// 2^kGrabShift to the caller's cursor, whose bits below kGrabShift count the
+// entries (a delta never reaches 2^36 entries): the old value's high bits
+// number the chunk, every reservation masks them off, and the block whose
+// grab is the last of all (each block's last grab finds no chunk) takes
+// them out again.
 constexpr int64_t kTailDiv = 16;
-constexpr int64_t kMaxTailTiles = (int64_t)1 << 20;
+constexpr int64_t kTailSlots = 16 * kVec;
+constexpr int64_t kMaxTailSlots = (int64_t)1 << 23;
 constexpr int kGrabShift = 36;
 constexpr unsigned long long kCountMask = (1ull << kGrabShift) - 1;
 
-__host__ __device__ inline int64_t tail_tiles(int64_t tiles, int64_t waves, bool dynamic)
+__device__ inline int64_t tail_slots(int64_t slots, int64_t waves)
 {
-    const int64_t d = dynamic && tiles >= kTailDiv * waves ? tiles / kTailDiv : 0;
-    return d < kMaxTailTiles ? d : kMaxTailTiles;
+    const int64_t d = slots >= kTailSlots * waves ? slots / kTailDiv : 0;
+    return d < kMaxTailSlots ? d : kMaxTailSlots;
 }
-// Per-wave LDS areas.  Keys are (wave iteration << kTileBits) | element in
-// the tile; the wave's tiles are t_first + iteration.
+
+// Per-wave LDS areas.  Keys are element offsets from element `base` of the
+// range: the wave's first element, in the dynamic tail the tail's.
 struct WaveStage {
     uint32_t* key;    // output staging: changed entries awaiting a flush
     uint16_t* val;
-    float* qp;        // candidate queue: elements without an "unchanged" proof
-    float* qm;
-    float* qv;
-    uint32_t* qkey;
-    int64_t t_first;
+    f32x4* queue;     // candidates, elements without an "unchanged" proof: p, m, v, key
+    int64_t base;
     int32_t wave;     // global wave number
 };
 
@@ -221,6 +237,7 @@ struct WaveStage {
 struct Staging {
     int staged;
     int64_t flushed;
+    int64_t met;        // entries staged in all at the block's last meeting
     int64_t in_region;
     int spilled;
 };
@@ -239,12 +256,11 @@ template <bool kStream>
 __device__ __forceinline__ void write_out(const ExtractParams& a, const WaveStage& st, int64_t base,
                                           int staged, int lane)
 {
+    const int64_t x0 = a.index_base + st.base;
     for (int i = lane; i < staged; i += 64) {
         const int64_t pos = base + i;
         if (pos < a.capacity) {
-            const uint32_t key = st.key[i];
-            const int64_t t = st.t_first + (int64_t)(key >> kTileBits);
-            const int64_t x = a.index_base + t * kWaveTile + (int64_t)(key & (kWaveTile - 1));
+            const int64_t x = x0 + (int64_t)st.key[i];
             if (kStream)
                 __builtin_nontemporal_store(x, a.out_idx + pos);
             else
@@ -264,7 +280,7 @@ __device__ __forceinline__ void write_staged(const ExtractParams& a, const WaveS
 {
     const int staged = so.staged;
     const uint32_t last = __builtin_amdgcn_readfirstlane(st.key[staged - 1]);
-    const int64_t scanned = ((int64_t)(last >> kTileBits) + 1) * kWaveTile;
+    const int64_t scanned = (int64_t)last + 1;
     if ((so.flushed + staged) * kDenseRatio > scanned)
         write_out<true>(a, st, base, staged, lane);
     else
@@ -283,8 +299,6 @@ __device__ void flush_wave(const ExtractParams& a, const WaveStage& st, Staging&
     const int staged = so.staged;
     wave_sync();   // every lane's LDS stores visible to the other lanes
     if (kRoute) {
-        if (lane == 0)
-            atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor), (unsigned long long)staged);
         rt::SegInfo cache{};
         int runv = 0;                            // lane r: entries for rank out.first + r
 #pragma unroll 1
@@ -303,9 +317,7 @@ __device__ void flush_wave(const ExtractParams& a, const WaveStage& st, Staging&
                 int64_t x = -1;
                 uint16_t y = 0;
                 if (i < staged) {
-                    const uint32_t key = st.key[i];
-                    const int64_t t = st.t_first + (int64_t)(key >> kTileBits);
-                    x = a.index_base + t * kWaveTile + (key & (kWaveTile - 1));
+                    x = a.index_base + st.base + (int64_t)st.key[i];
                     y = st.val[i];
                     if (x >= a.plan.total) x = -1;
                 }
@@ -326,9 +338,7 @@ __device__ void flush_wave(const ExtractParams& a, const WaveStage& st, Staging&
             // that every wave takes from one address slow the whole stream)
             const int64_t r0 = (int64_t)st.wave * a.region_size + so.flushed;
             for (int i = lane; i < staged; i += 64) {
-                const uint32_t key = st.key[i];
-                const int64_t t = st.t_first + (int64_t)(key >> kTileBits);
-                a.region_idx[r0 + i] = a.index_base + t * kWaveTile + (key & (kWaveTile - 1));
+                a.region_idx[r0 + i] = a.index_base + st.base + (int64_t)st.key[i];
                 a.region_val[r0 + i] = st.val[i];
             }
             so.flushed += staged;
@@ -384,10 +394,12 @@ __device__ __forceinline__ Slot4 select4(const bool (&sel)[4])
 // this lane's first selected element; its others follow in element order.
 __device__ __forceinline__ int lanes_before(const Slot4& r)
 {
-    int before = 0;
+    uint32_t before = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) before += lane_prefix(r.ball[k]);
-    return before;
+    for (int k = 0; k < 4; ++k)
+        before = __builtin_amdgcn_mbcnt_hi((uint32_t)(r.ball[k] >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)r.ball[k], before));
+    return (int)before;
 }
 
 // Stage one ballot of changed entries (at most 64), flushing first when the
@@ -421,9 +433,9 @@ __device__ __forceinline__ void stage_changed(const ExtractParams& a, const Wave
     so.staged = before + cnt - kWaveStage;
 }
 
-// Combined flushes of the unordered call.  Every kRound tiles, and once at
-// the end, the kW waves of a block meet at a barrier; when they hold at
-// least kBlockFlush staged entries (at the end: any), one atomicAdd on the
+// Combined flushes of the unordered call.  Every kRound passes over the ring
+// (fewer in dense ranges), and once at the end, the waves of a block meet at a barrier; when they hold at
+// least kFlushPerWave entries per wave (at the end: any), one atomicAdd on the
 // cursor reserves room for all of them and each wave writes its entries
 // after those of the waves before it.  Every wave of the device reserving
 // its own space from the one cursor address is what slows the stream (the
@@ -434,256 +446,296 @@ __device__ __forceinline__ void stage_changed(const ExtractParams& a, const Wave
 constexpr int kRound = 4;
 constexpr int kFlushPerWave = 768;            // block flush threshold per wave
 
-template <int kW>
-__device__ void block_round(const ExtractParams& a, const WaveStage& st, Staging& so, int lane,
-                            int wave, int (*s_cnt)[kW], unsigned long long* s_base, int slot,
-                            bool last_round)
+// Returns the number of passes until the next meeting: as many (up to
+// kRound) as leave room for what the block's waves found per pass since the
+// last one on top of kFlushPerWave entries, so that dense deltas rarely
+// make a wave flush on its own.
+__device__ int block_round(const ExtractParams& a, const WaveStage& st, Staging& so, int lane,
+                           int wave, int (*s_cnt)[kWaves], unsigned long long* s_base, int slot,
+                           int passes, bool last_round)
 {
-    if (lane == 0) s_cnt[slot][wave] = so.staged;
+    // (at most kRound * kVec * kSlot entries found: 16 bits each)
+    const int64_t all = so.flushed + so.staged;
+    if (lane == 0) s_cnt[slot][wave] = so.staged | ((int)(all - so.met) << 16);
+    so.met = all;
     __syncthreads();
-    int total = 0, before = 0;
+    int total = 0, before = 0, found = 0;
 #pragma unroll
-    for (int w = 0; w < kW; ++w) {
-        const int c = s_cnt[slot][w];
-        total += c;
-        before += w < wave ? c : 0;
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_cnt[slot][w];
+        const int staged = c & 0xFFFF;
+        total += staged;
+        found += c >> 16;
+        before += w < wave ? staged : 0;
     }
-    if (total == 0 || (!last_round && total < kW * kFlushPerWave)) return;
+    total = __builtin_amdgcn_readfirstlane(total);   // scalar: keeps the control flow uniform
+    found = __builtin_amdgcn_readfirstlane(found);
+    constexpr int kRoom = kWaves * (kWaveStage - kFlushPerWave);
+    int next = kRound;
+    while (next > 1 && next * found > kRoom * passes) next >>= 1;
+    if (total == 0 || (!last_round && total < kWaves * kFlushPerWave)) return next;
     if (threadIdx.x == 0)
         s_base[slot] = atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
                                  (unsigned long long)total) & kCountMask;
     __syncthreads();
     if (so.staged > 0) write_staged(a, st, so, (int64_t)s_base[slot] + before, lane);
+    return next;
 }
 
-// Exact inverse of every queued candidate, 64 per pass; changed ones are
-// staged.  Empties the queue.
+// Exact inverse of the first `count` queued candidates, 64 per pass; changed
+// ones are staged.  The rest (fewer than 64) move to the queue's front.
 template <bool kDecayOne, bool kLit, bool kRoute>
-__device__ void drain_queue(const ExtractParams& a, const WaveStage& st, int& queued, Staging& so,
-                            int lane)
+__device__ void drain_queue(const ExtractParams& a, const WaveStage& st, int& queued, int count,
+                            Staging& so, int lane)
 {
     wave_sync();
-    for (int base = 0; base < queued; base += 64) {
+    for (int base = 0; base < count; base += 64) {
         const int i = base + lane;
         bool changed = false;
         uint32_t key = 0;
         uint16_t bn = 0;
-        if (i < queued) {
-            const float p = st.qp[i];
-            const float ph = exact_prev<kDecayOne, kLit>(p, st.qm[i], st.qv[i], a);
-            bn = (uint16_t)bf16_bits(p);
+        if (i < count) {
+            const f32x4 c = st.queue[i];
+            const float ph = exact_prev<kDecayOne, kLit>(c.x, c.y, c.z, a);
+            bn = (uint16_t)bf16_bits(c.x);
             changed = bf16_bits(ph) != bn;
-            key = st.qkey[i];
+            key = __float_as_uint(c.w);
         }
         stage_changed<kRoute>(a, st, so, lane, changed, key, bn);
     }
-    queued = 0;
+    queued -= count;
+    if (queued > 0) {
+        f32x4 c = {};
+        if (lane < queued) c = st.queue[count + lane];
+        wave_sync();
+        if (lane < queued) st.queue[lane] = c;
+    }
     wave_sync();
 }
 
-// One wave tile of kWaveTile elements starting at element t0 of the range.
-// kFull: the tile lies inside [0, n) (no per-element bounds tests).
-template <bool kFull, bool kVecLoads>
-__device__ __forceinline__ void load_tile(const ExtractParams& a, int64_t t0, int lane,
-                                          f32x4* P, f32x4* M, f32x4* V)
+// What a wave loads in place of a slot beyond its last one.
+__device__ const f32x4 g_pad = {};
+
+// The float4 of each lane in the whole slot at element e0 of the range, or
+// (one request for the wave) the pad: loads are issued on every path, so that the number of loads in
+// flight behind a slot's own is known where the slot is tested.  Element
+// alignment is enough for 16-byte global loads.
+__device__ __forceinline__ void load_slot(const ExtractParams& a, bool valid, int64_t e0, int lane,
+                                          f32x4& P, f32x4& M, f32x4& V)
 {
-    const float* tp = a.p + t0;
-    const float* tm = a.m + t0;
-    const float* tv = a.v + t0;
-    const int64_t rem = a.n - t0;
+    // addresses as integers, cast to the global address space: a choice of
+    // two pointers would become flat loads, which wait for LDS as well
+    const uint64_t pad = (uint64_t)&g_pad, at = (uint64_t)e0 * sizeof(float);
+    const uint64_t p = valid ? (uint64_t)a.p + at : pad;
+    const uint64_t m = valid ? (uint64_t)a.m + at : pad;
+    const uint64_t v = valid ? (uint64_t)a.v + at : pad;
+    const int off = lane * 4 & (valid ? -1 : 0);
+    P = __builtin_nontemporal_load((global_f32x4)((global_f32)p + off));
+    M = __builtin_nontemporal_load((global_f32x4)((global_f32)m + off));
+    V = __builtin_nontemporal_load((global_f32x4)((global_f32)v + off));
+}
+
+// Stage the slot's selected elements that land in [from, to) of the staging
+// area when counted from `first`, at their place - from.
+__device__ __forceinline__ void stage_slot(const WaveStage& st, int first, int from, int to,
+                                           const Slot4& r, const bool (&sel)[4], uint32_t key,
+                                           const f32x4& P)
+{
+    int pos = first + lanes_before(r);
 #pragma unroll
-    for (int j = 0; j < kVec; ++j) {
-        const int off = (j * 64 + lane) * 4;
-        if (kFull) {
-            P[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(tp + off));
-            M[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(tm + off));
-            V[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(tv + off));
-        } else {
-            P[j] = load4<kVecLoads>(tp, off, rem);
-            M[j] = load4<kVecLoads>(tm, off, rem);
-            V[j] = load4<kVecLoads>(tv, off, rem);
+    for (int c = 0; c < 4; ++c) {
+        if (sel[c] && pos >= from && pos < to) {
+            st.key[pos - from] = key + c;
+            st.val[pos - from] = (uint16_t)bf16_bits(P[c]);
         }
+        pos += sel[c] ? 1 : 0;
     }
 }
 
-template <bool kFull, bool kVecLoads, bool kDecayOne, bool kWritePrev, bool kLit, bool kRoute>
-__device__ __forceinline__ void process_tile(const ExtractParams& a, int64_t t0, int lane,
-                                             Staging& so, int& queued, const WaveStage& st,
-                                             uint32_t iter, const f32x4* P, const f32x4* M,
-                                             const f32x4* V)
+// One slot, at element e0 of the range.  kPrev: the exact inverse of every
+// element, theta_hat written and changed elements staged; else the elements
+// without a proof join the queue, which is drained of whole groups of 64.
+// kEdge: the slot holds elements [e0, n) only.
+template <bool kEdge, bool kDecayOne, bool kPrev, bool kLit, bool kRoute>
+__device__ __forceinline__ void test_slot(const ExtractParams& a, const WaveStage& st,
+                                          Staging& so, int& queued, int lane, int64_t e0,
+                                          const f32x4& P, const f32x4& M, const f32x4& V)
 {
-    const int64_t rem = a.n - t0;
+    const int64_t e = e0 + lane * 4;
+    const uint32_t key = (uint32_t)(e0 - st.base) + lane * 4;
+    bool sel[4];
+    f32x4 prev;
 #pragma unroll
-    for (int j = 0; j < kVec; ++j) {
-        const int off = (j * 64 + lane) * 4;
-        const uint32_t key0 = (iter << kTileBits) | (uint32_t)off;
-        if (kWritePrev) {
-            // theta_hat requested: the exact path for every element
-            f32x4 prev;
-            bool sel[4];
-            uint32_t bn[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float p = P[j][c];
-                const float ph = exact_prev<kDecayOne, kLit>(p, M[j][c], V[j][c], a);
-                prev[c] = ph;
-                bn[c] = bf16_bits(p);
-                sel[c] = (kFull || off + c < rem) && bf16_bits(ph) != bn[c];
-            }
-            const Slot4 r = select4(sel);
-            if (r.count != 0) {
-                const int before = so.staged;
-                const int base = before + lanes_before(r);
-                int k = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (sel[c]) {
-                        if (base + k < kWaveStage) {
-                            st.key[base + k] = key0 + c;
-                            st.val[base + k] = (uint16_t)bn[c];
-                        }
-                        ++k;
-                    }
-                }
-                if (before + r.count < kWaveStage) {
-                    so.staged = before + r.count;
-                } else {   // full: flush one whole block, then stage the rest
-                    so.staged = kWaveStage;
-                    flush_wave<kRoute>(a, st, so, lane);
-                    k = 0;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        if (sel[c]) {
-                            if (base + k >= kWaveStage) {
-                                st.key[base + k - kWaveStage] = key0 + c;
-                                st.val[base + k - kWaveStage] = (uint16_t)bn[c];
-                            }
-                            ++k;
-                        }
-                    }
-                    so.staged = before + r.count - kWaveStage;
-                }
-            }
-            if (kFull || (kVecLoads && off + 3 < rem)) {
-                __builtin_nontemporal_store(prev, reinterpret_cast<f32x4*>(a.out_prev + t0 + off));
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (off + c < rem) a.out_prev[t0 + off + c] = prev[c];
-            }
+    for (int c = 0; c < 4; ++c) {
+        if (kPrev) {
+            prev[c] = exact_prev<kDecayOne, kLit>(P[c], M[c], V[c], a);
+            sel[c] = bf16_bits(prev[c]) != bf16_bits(P[c]);
         } else {
-            bool sel[4];
+            sel[c] = (kLit && !a.lit_filter) ||
+                     !proven_unchanged<kDecayOne, kLit>(P[c], M[c], V[c], a);
+        }
+        if (kEdge) sel[c] = sel[c] && e + c < a.n;
+    }
+    const Slot4 r = select4(sel);
+    if (kPrev) {
+        if (r.count != 0) {
+            const int first = so.staged, end = first + r.count;
+            stage_slot(st, first, 0, kWaveStage, r, sel, key, P);
+            so.staged = end;
+            if (end >= kWaveStage) {   // flush exactly kWaveStage entries, then stage the rest
+                so.staged = kWaveStage;
+                flush_wave<kRoute>(a, st, so, lane);
+                stage_slot(st, first, kWaveStage, end, r, sel, key, P);
+                so.staged = end - kWaveStage;
+            }
+        }
+        if (!kEdge) {
+            __builtin_nontemporal_store(prev, reinterpret_cast<f32x4_any*>(a.out_prev + e));
+        } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                sel[c] = (kFull || off + c < rem) &&
-                         ((kLit && !a.lit_filter) ||
-                          !proven_unchanged<kDecayOne, kLit>(P[j][c], M[j][c], V[j][c], a));
-            const Slot4 r = select4(sel);
-            if (r.count != 0) {
-                if (queued + r.count > kQueue)
-                    drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, so, lane);
-                const int base = queued + lanes_before(r);
-                int k = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (sel[c]) {
-                        st.qp[base + k] = P[j][c];
-                        st.qm[base + k] = M[j][c];
-                        st.qv[base + k] = V[j][c];
-                        st.qkey[base + k] = key0 + c;
-                        ++k;
-                    }
-                }
-                queued += r.count;
-            }
+                if (e + c < a.n) a.out_prev[e + c] = prev[c];
         }
+    } else if (r.count != 0) {
+        int pos = queued + lanes_before(r);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (sel[c]) st.queue[pos] = f32x4{P[c], M[c], V[c], __uint_as_float(key + c)};
+            pos += sel[c] ? 1 : 0;
+        }
+        queued += r.count;
+        if (queued >= kDrain)
+            drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued & ~63, so, lane);
     }
 }
 
-// Wave tiles [first, last) of the range; kFull: each lies inside [0, n).
-template <bool kFull, bool kVecLoads, bool kDecayOne, bool kWritePrev, bool kLit, bool kRoute>
-__global__ __launch_bounds__(64 * kWavesOf<kFull>) void extract_kernel(ExtractParams a,
-                                                                      int64_t first, int64_t last)
+// One launch covers the range.  kFull: n is a multiple of kSlot.
+//
+// Bound by HBM (12 bytes read an element).  A wave streams its slots through
+// a ring of kVec slots in registers: as soon as slot s is tested, the loads
+// of slot s + kVec replace it, so loads stay in flight while the wave
+// computes.  (Loading eight slots, waiting for all and then testing all left
+// the memory idle while dense ranges computed, and tested the last slots of
+// odd ranges in a second launch.)  386 M elements of Qwen3-8B layers, before
+// -> now: lr 1e-6 697 -> 678 us, 1e-5 (2.3 % change) 805 -> 757, 1e-4 (13.8
+// %) 968 -> 883, odd bases 2285 -> 720.  Draining the queue after every slot
+// keeps room for any slot; the alternative, putting off and reloading slots
+// that find no room, took 2120 us at lr 1e-3 against 1338.
+template <bool kFull, bool kOneGroup, bool kDecayOne, bool kWritePrev, bool kLit, bool kRoute>
+__global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
 {
-    constexpr int kWaves = kWavesOf<kFull>;
     __shared__ uint32_t s_key[kWaves][kWaveStage];
     __shared__ uint16_t s_val[kWaves][kWaveStage];
-    __shared__ float s_qp[kWaves][kQueue];
-    __shared__ float s_qm[kWaves][kQueue];
-    __shared__ float s_qv[kWaves][kQueue];
-    __shared__ uint32_t s_qkey[kWaves][kQueue];
+    __shared__ f32x4 s_queue[kWaves][kQueue];
     __shared__ int s_cnt[2][kWaves];
     __shared__ unsigned long long s_base[2];
-    __shared__ int64_t s_chunk;
+    __shared__ unsigned long long s_chunk;
 
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t g = (int64_t)blockIdx.x * kWaves + wave;
     const int64_t nw = (int64_t)gridDim.x * kWaves;
     // unordered output: combined flushes (block_round); every wave of the
     // block runs the same iterations, so the barriers match
     const bool combine = !kRoute && a.runs == nullptr;
-    // wave g owns the contiguous tile range [g per, (g+1) per) of the
-    // static part [first, s_last); the tail [s_last, last) is dynamic
-    constexpr bool kTail = kFull && !kRoute;     // a dynamic tail is possible
-    const int64_t tail = kTail ? tail_tiles(last - first, nw, combine) : 0;
-    const int64_t s_last = last - tail;
-    const int64_t per = (s_last - first + nw - 1) / nw;
-    const int64_t w_first = first + g * per;
-    const int64_t w_last = (w_first + per < s_last) ? w_first + per : s_last;
-    Staging so{0, 0, 0, 0};
-    const WaveStage st{s_key[wave], s_val[wave], s_qp[wave], s_qm[wave], s_qv[wave],
-                       s_qkey[wave], w_first, a.wave0 + (int32_t)g};
+    // wave g owns slots [g per, (g+1) per) of the static part [0, s_last);
+    // the tail [s_last, slots) is dynamic
+    const int64_t slots = (a.n + kSlot - 1) / kSlot, whole = a.n / kSlot;
+    const int64_t tail = combine ? tail_slots(slots, nw) : 0;
+    const int64_t s_last = slots - tail;
+    const int64_t per = (s_last + nw - 1) / nw;
+    Staging so{0, 0, 0, 0, 0};
+    WaveStage st{s_key[wave], s_val[wave], s_queue[wave], g * per * kSlot, (int32_t)g};
     int queued = 0;
     int round = 0;                               // block_round calls so far (LDS slot parity)
-    for (int64_t it = 0; it < per; ++it) {
-        const int64_t t = w_first + it;
-        if (t < w_last) {
-            f32x4 P[kVec], M[kVec], V[kVec];
-            load_tile<kFull, kVecLoads>(a, t * kWaveTile, lane, P, M, V);
-            process_tile<kFull, kVecLoads, kDecayOne, kWritePrev, kLit, kRoute>(
-                a, t * kWaveTile, lane, so, queued, st, (uint32_t)it, P, M, V);
+    int passes = kRound, togo = kRound;          // passes between meetings, until the next
+    bool in_tail = false;
+    int64_t first = g * per;
+    int64_t last = first + per < s_last ? first + per : s_last;
+    int64_t iters = (per + kVec - 1) / kVec;     // passes over the ring
+    int64_t it = -1;                             // pass -1 only fills it
+    f32x4 P[kVec], M[kVec], V[kVec];
+    for (;;) {
+        const int64_t s0 = first + it * kVec;
+        const int64_t rest = (last < whole ? last : whole) - s0;
+        const int left = (int)(rest < 2 * kVec ? rest : 2 * kVec);   // whole slots from s0
+#pragma unroll
+        for (int j = 0; j < kVec; ++j) {
+            const int64_t e0 = (s0 + j) * kSlot;
+            if (it >= 0 && j < left)
+                test_slot<false, kDecayOne, kWritePrev, kLit, kRoute>(a, st, so, queued, lane, e0,
+                                                                      P[j], M[j], V[j]);
+            load_slot(a, j + kVec < left, e0 + kVec * kSlot, lane, P[j], M[j], V[j]);
         }
-        if (it % kRound == kRound - 1) {
+        ++it;
+        if (it > 0 && --togo == 0) {
+            togo = kRound;
             if (combine)
-                block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1, false);
+                togo = passes = block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1,
+                                            passes, false);
             else if (!kRoute)
                 __syncthreads();   // ordered: keeps the block's waves in step
         }
-    }
-    if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, so, lane);
-    if (kTail && tail > 0) {
-        // staged keys count tiles from the stage's first tile: empty the
-        // staging areas, then count from the tail's start
-        block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1, true);
-        const WaveStage tst{s_key[wave], s_val[wave], s_qp[wave], s_qm[wave], s_qv[wave],
-                            s_qkey[wave], s_last, st.wave};
-        for (;;) {
-            if (threadIdx.x == 0)
-                s_chunk = (int64_t)(atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
-                                              1ull << kGrabShift) >> kGrabShift);
-            __syncthreads();
-            const int64_t c = s_chunk * (kWaves * kRound);   // block-uniform
-            __syncthreads();                                 // s_chunk is rewritten next
-            if (c >= tail) break;
-            for (int i = 0; i < kRound; ++i) {
-                const int64_t rel = c + (int64_t)wave * kRound + i;   // tile s_last + rel
-                if (rel < tail) {
-                    f32x4 P[kVec], M[kVec], V[kVec];
-                    load_tile<kFull, kVecLoads>(a, (s_last + rel) * kWaveTile, lane, P, M, V);
-                    process_tile<kFull, kVecLoads, kDecayOne, kWritePrev, kLit, kRoute>(
-                        a, (s_last + rel) * kWaveTile, lane, so, queued, tst, (uint32_t)rel, P,
-                        M, V);
+        if (it < iters) continue;
+        if (!kFull && first <= whole && whole < last) {      // the range's partial slot
+            f32x4 p = {}, m = {}, v = {};
+            const int64_t e = whole * kSlot + lane * 4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (e + c < a.n) {
+                    p[c] = a.p[e + c];
+                    m[c] = a.m[e + c];
+                    v[c] = a.v[e + c];
                 }
             }
-            block_round(a, tst, so, lane, wave, s_cnt, s_base, (round++) & 1, false);
+            test_slot<true, kDecayOne, kWritePrev, kLit, kRoute>(a, st, so, queued, lane,
+                                                                 whole * kSlot, p, m, v);
         }
-        if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, tst, queued, so, lane);
-        block_round(a, tst, so, lane, wave, s_cnt, s_base, (round++) & 1, true);
-    } else if (combine) {
-        block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1, true);
-    } else if (so.staged > 0) {
+        if (tail == 0) break;
+        if (!in_tail) {
+            // staged keys count from the stage's base: empty the queue and
+            // the staging areas, then count from the tail's start
+            if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued, so, lane);
+            togo = passes = block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1,
+                                        passes, true);
+            st.base = s_last * kSlot;
+            in_tail = true;
+        }
+        constexpr int64_t kWaveChunk = kRound * kVec, kChunk = kWaves * kWaveChunk;
+        if (threadIdx.x == 0)
+            s_chunk = atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
+                                1ull << kGrabShift) >> kGrabShift;
+        __syncthreads();
+        const int64_t chunk = rt::readlane64((int64_t)s_chunk, 0);   // block-uniform
+        __syncthreads();                                     // s_chunk is rewritten next
+        if (chunk * kChunk >= tail) {
+            // chunks and one empty grab per block: the last of them clears
+            // the grab count
+            const int64_t grabs = (tail + kChunk - 1) / kChunk + gridDim.x;
+            if (threadIdx.x == 0 && chunk == grabs - 1)
+                atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
+                          0ull - ((unsigned long long)grabs << kGrabShift));
+            break;
+        }
+        first = s_last + chunk * kChunk + wave * kWaveChunk;
+        last = first + kWaveChunk < slots ? first + kWaveChunk : slots;
+        iters = kRound;
+        it = -1;
+    }
+    if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued, so, lane);
+    if (combine)
+        block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1, passes, true);
+    else if (so.staged > 0)
         flush_wave<kRoute>(a, st, so, lane);
+    if (kRoute) {   // one addition of the entry count per block, not one per flush
+        if (lane == 0) s_cnt[0][wave] = (int)so.flushed;
+        __syncthreads();
+        if (wave == 0) {
+            unsigned long long n = lane < kWaves ? (unsigned)s_cnt[0][lane] : 0u;
+            for (int d = 8; d > 0; d >>= 1) n += __shfl_down(n, d);
+            if (lane == 0 && n > 0)
+                atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor), n);
+        }
     }
     if (a.runs && lane == 0) {
         a.wave_count[st.wave] = so.flushed;
@@ -734,61 +786,37 @@ __global__ __launch_bounds__(256) void adamw_forward_kernel(ForwardParams a)
     }
 }
 
-// After an unordered launch with a dynamic tail: the grab count leaves the
-// cursor's high bits (single thread; runs after the extract kernel on the
-// same stream).
-__global__ void clear_grabs_kernel(int64_t* cursor)
-{
-    *cursor = (int64_t)((unsigned long long)*cursor & kCountMask);
-}
-
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Blocks that one launch over wave tiles [first, last) uses, at most
-// max_waves waves.
-template <bool F>
-int64_t blocks_of(int64_t first, int64_t last, int64_t max_waves)
+template <bool F, bool D, bool L, bool R>
+void launch_kernel(const ExtractParams& a, dim3 grid, hipStream_t s)
 {
-    if (last <= first) return 0;
-    const int64_t b = (last - first + kWavesOf<F> - 1) / kWavesOf<F>;
-    const int64_t cap = max_waves / kWavesOf<F>;
+    const dim3 block(64 * kWaves);
+    if (R)   // routing mode: no theta_hat output
+        hipLaunchKernelGGL((extract_kernel<F, true, D, false, L, R>), grid, block, 0, s, a);
+    else if (a.out_prev)
+        hipLaunchKernelGGL((extract_kernel<F, true, D, true, L, false>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((extract_kernel<F, true, D, false, L, false>), grid, block, 0, s, a);
+}
+
+// Blocks of one call: a slot per wave at least, one block per CU at most.
+int64_t blocks_of(int64_t n, int cus)
+{
+    const int64_t slots = (n + kSlot - 1) / kSlot;
+    const int64_t b = (slots + kWaves * kMinSlots - 1) / (kWaves * kMinSlots);
+    const int64_t cap = cus < kMaxWaves / kWaves ? cus : kMaxWaves / kWaves;
     return b < cap ? b : cap;
 }
 
-// Launch over wave tiles [first, last); returns the number of waves.
-template <bool F, bool V, bool D, bool L, bool R>
-int32_t launch_tiles(ExtractParams a, int64_t first, int64_t last, int64_t max_waves,
-                     int32_t wave0, hipStream_t s)
-{
-    if (last <= first) return 0;
-    constexpr int kBlock = 64 * kWavesOf<F>;
-    const dim3 grid((unsigned)blocks_of<F>(first, last, max_waves));
-    a.wave0 = wave0;
-    if (R)   // routing mode: no theta_hat output
-        hipLaunchKernelGGL((extract_kernel<F, V, D, false, L, R>), grid, dim3(kBlock), 0, s, a, first,
-                           last);
-    else if (a.out_prev)
-        hipLaunchKernelGGL((extract_kernel<F, V, D, true, L, false>), grid, dim3(kBlock), 0, s, a,
-                           first, last);
-    else
-        hipLaunchKernelGGL((extract_kernel<F, V, D, false, L, false>), grid, dim3(kBlock), 0, s, a,
-                           first, last);
-    if (F && !R && a.runs == nullptr &&
-        tail_tiles(last - first, (int64_t)grid.x * kWavesOf<F>, true) > 0)
-        hipLaunchKernelGGL(clear_grabs_kernel, dim3(1), dim3(1), 0, s, a.cursor);
-    return (int32_t)grid.x * kWavesOf<F>;
-}
-
 template <bool D, bool L, bool R>
-int32_t launch_all(const ExtractParams& a, bool vec, int64_t max_waves, hipStream_t s)
+void launch_range(const ExtractParams& a, int cus, hipStream_t s)
 {
-    const int64_t full = a.n / kWaveTile;
-    const int64_t ntiles = (a.n + kWaveTile - 1) / kWaveTile;
-    if (vec) {
-        const int32_t w = launch_tiles<true, true, D, L, R>(a, 0, full, max_waves, 0, s);  // unguarded
-        return w + launch_tiles<false, true, D, L, R>(a, full, ntiles, max_waves, w, s);   // ragged
-    }
-    return launch_tiles<false, false, D, L, R>(a, 0, ntiles, max_waves, 0, s);           // scalar loads
+    const dim3 grid((unsigned)blocks_of(a.n, cus));
+    if (a.n % kSlot == 0)
+        launch_kernel<true, D, L, R>(a, grid, s);
+    else
+        launch_kernel<false, D, L, R>(a, grid, s);
 }
 
 // ---- ordered mode: runs to ascending positions ----------------------------
@@ -893,65 +921,26 @@ hipError_t launch_order(const OrderParams& o, int cus, hipStream_t stream)
     return hipGetLastError();
 }
 
-namespace {
+int64_t extract_waves(int64_t n, int cus) { return n > 0 ? blocks_of(n, cus) * kWaves : 0; }
 
-// Waves that launch_all launches (its grid rule).
-int64_t waves_of(int64_t n, bool vec, int64_t max_waves)
+hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream)
 {
-    const int64_t full = n / kWaveTile;
-    const int64_t ntiles = (n + kWaveTile - 1) / kWaveTile;
-    if (vec)
-        return blocks_of<true>(0, full, max_waves) * kWavesOf<true> +
-               blocks_of<false>(full, ntiles, max_waves) * kWavesOf<false>;
-    return blocks_of<false>(0, ntiles, max_waves) * kWavesOf<false>;
-}
-
-// Waves per launch at most.  Ordered mode: both launches together stay
-// within kMaxOrderedWaves (the ragged launch covers one tile: one block).
-int64_t max_waves_of(const ExtractParams& a, int cus)
-{
-    int64_t max_waves = (int64_t)cus * kWavesPerCU;
-    const int64_t ordered_cap = kMaxOrderedWaves - kWavesOf<false>;
-    if (a.runs && max_waves > ordered_cap) max_waves = ordered_cap;
-    return max_waves;
-}
-
-bool vector_loads(const ExtractParams& a)
-{
-    return aligned16(a.p) && aligned16(a.m) && aligned16(a.v) &&
-           (a.out_prev == nullptr || aligned16(a.out_prev));
-}
-
-}  // namespace
-
-int64_t extract_waves(const ExtractParams& a, int cus)
-{
-    return a.n > 0 ? waves_of(a.n, vector_loads(a), max_waves_of(a, cus)) : 0;
-}
-
-hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream, int32_t* waves)
-{
-    if (waves) *waves = 0;
     if (a.n <= 0) return hipSuccess;
-    const int64_t max_waves = max_waves_of(a, cus);
-    const bool vec = vector_loads(a);
-    int32_t w;
     const bool one = a.decay == 1.0f;
     if (a.route) {
         if (a.literal)
-            w = one ? launch_all<true, true, true>(a, vec, max_waves, stream)
-                    : launch_all<false, true, true>(a, vec, max_waves, stream);
+            one ? launch_range<true, true, true>(a, cus, stream)
+                : launch_range<false, true, true>(a, cus, stream);
         else
-            w = one ? launch_all<true, false, true>(a, vec, max_waves, stream)
-                    : launch_all<false, false, true>(a, vec, max_waves, stream);
+            one ? launch_range<true, false, true>(a, cus, stream)
+                : launch_range<false, false, true>(a, cus, stream);
     } else if (a.literal) {
-        w = one ? launch_all<true, true, false>(a, vec, max_waves, stream)
-                : launch_all<false, true, false>(a, vec, max_waves, stream);
+        one ? launch_range<true, true, false>(a, cus, stream)
+            : launch_range<false, true, false>(a, cus, stream);
     } else {
-        w = one ? launch_all<true, false, false>(a, vec, max_waves, stream)
-                : launch_all<false, false, false>(a, vec, max_waves, stream);
+        one ? launch_range<true, false, false>(a, cus, stream)
+            : launch_range<false, false, false>(a, cus, stream);
     }
-    if (waves) *waves = w;
     return hipGetLastError();
 }
 
