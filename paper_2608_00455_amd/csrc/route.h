@@ -51,6 +51,16 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int lane)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// The plan's tables are read-only while kernels run: through the constant
+// address space, uniform indexes become scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* constant(const T* p)
+{
+    return (const __attribute__((address_space(4))) T*)(uint64_t)p;
+}
+
+__device__ __forceinline__ int64_t uniform64(int64_t x) { return readlane64(x, 0); }
+
 // Wave-uniform description of the current segment (scalar registers).
 struct SegInfo {
     int64_t lo, hi;      // flat range [lo, hi); empty before the first lookup
@@ -62,29 +72,31 @@ struct SegInfo {
 // Segment holding the uniform flat offset i0 (0 <= i0 < total).
 __device__ __forceinline__ SegInfo find_segment(const PlanView& pl, int64_t i0)
 {
-    int32_t s = __builtin_amdgcn_readfirstlane(pl.lookup[i0 >> pl.shift]);
-    while (readlane64(pl.seg_begin[s + 1], 0) <= i0) ++s;
+    i0 = uniform64(i0);
+    const auto begin = constant(pl.seg_begin);
+    int32_t s = constant(pl.lookup)[i0 >> pl.shift];
+    while (begin[s + 1] <= i0) ++s;
     SegInfo g;
-    g.lo = readlane64(pl.seg_begin[s], 0);
-    g.hi = readlane64(pl.seg_begin[s + 1], 0);
+    g.lo = begin[s];
+    g.hi = begin[s + 1];
     g.seg = s;
-    g.k0 = __builtin_amdgcn_readfirstlane(pl.seg_ops[s]);
-    g.k1 = __builtin_amdgcn_readfirstlane(pl.seg_ops[s + 1]);
-    g.nd = __builtin_amdgcn_readfirstlane(pl.seg_ndim[s]);
+    g.k0 = constant(pl.seg_ops)[s];
+    g.k1 = constant(pl.seg_ops)[s + 1];
+    g.nd = constant(pl.seg_ndim)[s];
 #pragma unroll
     for (int d = 0; d < DTE_MAX_DIMS; ++d)
-        g.shape[d] = __builtin_amdgcn_readfirstlane(pl.seg_shape[(int64_t)s * DTE_MAX_DIMS + d]);
+        g.shape[d] = constant(pl.seg_shape)[(int64_t)s * DTE_MAX_DIMS + d];
     return g;
 }
 
-// One operation with every field made wave-uniform (scalar registers).
+// One operation, wave-uniform (scalar registers).
 __device__ __forceinline__ DevOp load_op(const DevOp* ops, int32_t k)
 {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(ops + k);
+    const auto w = constant(reinterpret_cast<const uint32_t*>(ops + __builtin_amdgcn_readfirstlane(k)));
     DevOp o;
     uint32_t* d = reinterpret_cast<uint32_t*>(&o);
 #pragma unroll
-    for (int i = 0; i < (int)(sizeof(DevOp) / 4); ++i) d[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    for (int i = 0; i < (int)(sizeof(DevOp) / 4); ++i) d[i] = w[i];
     return o;
 }
 
