@@ -567,7 +567,7 @@ dte_status dte_adamw_forward(float* p, float* m, float* v, const float* g, int64
     a.lr = sc.s.lr;
     a.bc1 = sc.s.bc1;
     a.bc2 = sc.s.bc2;
-    return dte::launch_adamw_forward(a, current_cus(), (hipStream_t)stream) == hipSuccess
+    return dte::launch_adamw_forward(a, (hipStream_t)stream) == hipSuccess
                ? DTE_OK
                : DTE_ERR_HIP;
 }

@@ -150,7 +150,7 @@ struct ForwardParams {
     int32_t literal;
 };
 
-hipError_t launch_adamw_forward(const ForwardParams& a, int cus, hipStream_t stream);
+hipError_t launch_adamw_forward(const ForwardParams& a, hipStream_t stream);
 
 hipError_t launch_zero_i64(int64_t* p, int64_t n, hipStream_t stream);
 

@@ -86,6 +86,14 @@ typedef f32x4 f32x4_any __attribute__((aligned(4)));   // element-aligned
 typedef const __attribute__((address_space(1))) f32x4_any* global_f32x4;
 typedef const __attribute__((address_space(1))) float* global_f32;
 
+constexpr int kForwardBlock = 256;
+constexpr int64_t kForwardBlocks = (int64_t)1 << 23;   // 2^31 threads, within a launch's limit
+// Elements above which the forward step goes past the caches: the last-level
+// cache (256 MB) holds the four arrays up to 2^24.  Through / past the
+// caches, us: 8 M 31.9 / 38.5, 16 M 60.6 / 82.5, 25 M 136 / 118, 50 M 269 /
+// 240, 193 M 984 / 891.
+constexpr int64_t kForwardStream = (int64_t)1 << 24;
+
 // Adaptive step term u = (lrb1*m) / (sqrt(v*rbc2) + eps): four binary32
 // operations, each rounded once (sqrt and divide correctly rounded).
 __device__ __forceinline__ float step_term(float m, float v, float lrb1, float rbc2, float eps)
@@ -120,21 +128,6 @@ __device__ __forceinline__ uint32_t bf16_bits(float x)
 }
 
 using rt::lane_prefix;   // set lanes of the mask below this lane
-
-template <bool kVecLoads>
-__device__ __forceinline__ f32x4 load4(const float* base, int64_t e, int64_t n)
-{
-    f32x4 r = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (kVecLoads && e + 3 < n) {
-        r = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base + e));
-    } else {
-        if (e + 0 < n) r.x = base[e + 0];
-        if (e + 1 < n) r.y = base[e + 1];
-        if (e + 2 < n) r.z = base[e + 2];
-        if (e + 3 < n) r.w = base[e + 3];
-    }
-    return r;
-}
 
 // True only if b(ph) == b(p) is proven without the exact inverse (see the
 // header).  B bounds |u| from above: hardware sqrt / reciprocal (about one
@@ -743,15 +736,44 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
     }
 }
 
-template <bool kVecLoads>
-__global__ __launch_bounds__(256) void adamw_forward_kernel(ForwardParams a)
+// One AdamW step.  Bound by HBM (16 bytes read, 12 written an element).  A
+// float4 of each array per lane, whatever the alignment, and as many blocks
+// as that takes: blocks that come and go keep reads and writes mixed, where a
+// persistent grid of 8 blocks per CU took 1231 us on 193 M elements against
+// 986 us, 891 us with loads and stores past the caches (kStream); 2 or 4
+// float4 per lane 951 / 932 us, contiguous ranges per block 1041-1095 us.
+template <bool kStream>
+__global__ __launch_bounds__(kForwardBlock) void adamw_forward_kernel(ForwardParams a)
 {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; e < a.n; e += stride) {
-        f32x4 P = load4<kVecLoads>(a.p, e, a.n);
-        f32x4 M = load4<kVecLoads>(a.m, e, a.n);
-        f32x4 V = load4<kVecLoads>(a.v, e, a.n);
-        const f32x4 G = load4<kVecLoads>(a.g, e, a.n);
+    const auto load = [&](const float* x, int64_t e) {
+        f32x4 r = {};
+        if (e + 3 < a.n) {
+            const global_f32x4 q = (global_f32x4)(x + e);
+            r = kStream ? __builtin_nontemporal_load(q) : *q;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (e + c < a.n) r[c] = x[e + c];
+        }
+        return r;
+    };
+    const auto store = [&](float* x, int64_t e, const f32x4& y) {
+        if (e + 3 < a.n) {
+            if (kStream)
+                __builtin_nontemporal_store(y, reinterpret_cast<f32x4_any*>(x + e));
+            else
+                *reinterpret_cast<f32x4_any*>(x + e) = y;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (e + c < a.n) x[e + c] = y[c];
+        }
+    };
+    const int64_t stride = (int64_t)gridDim.x * kForwardBlock * 4;
+    for (int64_t e = ((int64_t)blockIdx.x * kForwardBlock + threadIdx.x) * 4; e < a.n;
+         e += stride) {
+        f32x4 P = load(a.p, e), M = load(a.m, e), V = load(a.v, e);
+        const f32x4 G = load(a.g, e);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float g = G[c];
@@ -769,24 +791,11 @@ __global__ __launch_bounds__(256) void adamw_forward_kernel(ForwardParams a)
             M[c] = mt;
             V[c] = vt;
         }
-        if (kVecLoads && e + 3 < a.n) {
-            *reinterpret_cast<f32x4*>(a.p + e) = P;
-            *reinterpret_cast<f32x4*>(a.m + e) = M;
-            *reinterpret_cast<f32x4*>(a.v + e) = V;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (e + c < a.n) {
-                    a.p[e + c] = P[c];
-                    a.m[e + c] = M[c];
-                    a.v[e + c] = V[c];
-                }
-            }
-        }
+        store(a.p, e, P);
+        store(a.m, e, M);
+        store(a.v, e, V);
     }
 }
-
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 template <bool F, bool D, bool L, bool R>
 void launch_kernel(const ExtractParams& a, dim3 grid, hipStream_t s)
@@ -944,18 +953,16 @@ hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_adamw_forward(const ForwardParams& a, int cus, hipStream_t stream)
+hipError_t launch_adamw_forward(const ForwardParams& a, hipStream_t stream)
 {
     if (a.n <= 0) return hipSuccess;
     const int64_t quads = (a.n + 3) / 4;
-    const int64_t blocks = (quads + 255) / 256;
-    const int64_t want = (int64_t)cus * 8;
-    const dim3 grid((unsigned)(blocks < want ? blocks : want));
-    const bool vec = aligned16(a.p) && aligned16(a.m) && aligned16(a.v) && aligned16(a.g);
-    if (vec)
-        hipLaunchKernelGGL(adamw_forward_kernel<true>, grid, dim3(256), 0, stream, a);
+    const int64_t blocks = (quads + kForwardBlock - 1) / kForwardBlock;
+    const dim3 grid((unsigned)(blocks < kForwardBlocks ? blocks : kForwardBlocks));
+    if (a.n > kForwardStream)
+        hipLaunchKernelGGL(adamw_forward_kernel<true>, grid, dim3(kForwardBlock), 0, stream, a);
     else
-        hipLaunchKernelGGL(adamw_forward_kernel<false>, grid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(adamw_forward_kernel<false>, grid, dim3(kForwardBlock), 0, stream, a);
     return hipGetLastError();
 }
 
