@@ -285,6 +285,17 @@ dte_status dte_remap(const dte_plan* plan, const int64_t* idx, const uint16_t* v
                      uint16_t* const* out_val, const int64_t* rank_capacity,
                      int64_t* rank_count, void* stream);
 
+/* dte_remap and dte_apply in one pass: every entry that reaches a bucket is
+ * also stored to its receiver's shard.  Buckets, counts and shards end as
+ * after the two calls, except that rank_count is not cleared: the caller
+ * clears it before the call (entries are appended to the buckets at the
+ * counts found).  idx must not repeat an offset, as no delta of one step
+ * does.  Arguments and errors as in those two calls. */
+dte_status dte_remap_apply(const dte_plan* plan, const int64_t* idx, const uint16_t* val,
+                           const int64_t* count, int64_t in_capacity, int64_t* const* out_off,
+                           uint16_t* const* out_val, const int64_t* rank_capacity,
+                           int64_t* rank_count, uint16_t* const* shards, void* stream);
+
 /* dte_extract_delta and dte_remap in one pass (paper sec. 4.2.1: changed
  * indices are remapped as soon as they are detected): the changed entries
  * of [index_base, index_base + n) are routed through `plan` straight into
@@ -300,6 +311,16 @@ dte_status dte_extract_remap(const float* p, const float* m, const float* v, int
                              int64_t* const* out_off, uint16_t* const* out_val,
                              const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
                              void* stream);
+
+/* dte_extract_remap that also stores every entry that reaches a bucket to
+ * its receiver's shard (dte_apply of the call's own entries).  Arguments and
+ * errors as in dte_extract_remap and dte_apply. */
+dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v, int64_t n,
+                                   int64_t index_base, const dte_adamw_step* hp,
+                                   const dte_plan* plan, int64_t* const* out_off,
+                                   uint16_t* const* out_val, const int64_t* rank_capacity,
+                                   int64_t* rank_count, int64_t* count, uint16_t* const* shards,
+                                   void* stream);
 
 /* Direct sparse apply (paper sec. 4.3, eq. direct_sparse_apply):
  * shards[r][off[r][k]] = val[r][k] for k < min(rank_count[r],

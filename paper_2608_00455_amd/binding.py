@@ -19,8 +19,8 @@ DTE_MAX_RANKS = 64
 EXPORTED = ("dte_derive_scalars", "dte_extract_delta", "dte_ordered_workspace_bytes",
             "dte_extract_delta_ordered", "dte_extract_delta_ordered_noalloc",
             "dte_ordered_noalloc_max_capacity", "dte_plan_create", "dte_plan_destroy",
-            "dte_plan_info", "dte_remap", "dte_extract_remap", "dte_apply", "dte_adamw_forward",
-            "dte_status_string")
+            "dte_plan_info", "dte_remap", "dte_extract_remap", "dte_apply", "dte_remap_apply",
+            "dte_extract_remap_apply", "dte_adamw_forward", "dte_status_string")
 
 
 class DteError(RuntimeError):
@@ -105,6 +105,11 @@ def _lib():
         L.dte_extract_remap.argtypes = [P, P, P, I64, I64, ctypes.POINTER(dte_adamw_step), P,
                                         ctypes.POINTER(P), ctypes.POINTER(P), ctypes.POINTER(I64),
                                         P, P, P]
+        L.dte_remap_apply.restype = S
+        L.dte_remap_apply.argtypes = L.dte_remap.argtypes[:-1] + [ctypes.POINTER(P), P]
+        L.dte_extract_remap_apply.restype = S
+        L.dte_extract_remap_apply.argtypes = (L.dte_extract_remap.argtypes[:-1] +
+                                              [ctypes.POINTER(P), P])
         L.dte_apply.restype = S
         L.dte_apply.argtypes = [P, ctypes.POINTER(P), ctypes.POINTER(P), ctypes.POINTER(P), P,
                                 ctypes.POINTER(I64), P]
@@ -186,6 +191,14 @@ def dte_extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_c
                                     rank_count, count, stream or None))
 
 
+def dte_extract_remap_apply(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
+                            rank_count, count, shards, stream=0):
+    _check("dte_extract_remap_apply",
+           _lib().dte_extract_remap_apply(p, m, v, n, index_base, ctypes.byref(_hp(hp)), plan,
+                                          _ptrs(out_off), _ptrs(out_val), _i64s(rank_capacity),
+                                          rank_count, count, _ptrs(shards), stream or None))
+
+
 def dte_adamw_forward(p, m, v, g, n, hp, stream=0):
     _check("dte_adamw_forward",
            _lib().dte_adamw_forward(p, m, v, g, n, ctypes.byref(_hp(hp)), stream or None))
@@ -218,6 +231,14 @@ def dte_remap(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacit
     _check("dte_remap",
            _lib().dte_remap(plan, idx, val, count, in_capacity, _ptrs(out_off), _ptrs(out_val),
                             _i64s(rank_capacity), rank_count, stream or None))
+
+
+def dte_remap_apply(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacity,
+                    rank_count, shards, stream=0):
+    _check("dte_remap_apply",
+           _lib().dte_remap_apply(plan, idx, val, count, in_capacity, _ptrs(out_off),
+                                  _ptrs(out_val), _i64s(rank_capacity), rank_count,
+                                  _ptrs(shards), stream or None))
 
 
 def dte_apply(plan, shards, off, val, rank_count, rank_capacity, stream=0):

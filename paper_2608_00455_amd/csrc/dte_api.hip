@@ -685,6 +685,100 @@ dte_status plan_create(const dte_segment* segs, int32_t nseg, const dte_op* ops,
 
 }  // namespace
 
+namespace {
+
+// Buckets of ranks [first, first + count) for one launch, with the shards
+// that it applies to (shards != nullptr).
+dte::RankSlice rank_slice(const dte_plan* plan, int32_t first, int64_t* const* out_off,
+                          uint16_t* const* out_val, const int64_t* rank_capacity,
+                          uint16_t* const* shards)
+{
+    dte::RankSlice sl;
+    std::memset(&sl, 0, sizeof sl);
+    sl.first = first;
+    sl.count = std::min<int32_t>(dte::kRanksPerLaunch, plan->nranks - first);
+    for (int32_t r = 0; r < sl.count; ++r) {
+        sl.off[r] = out_off[first + r];
+        sl.val[r] = out_val[first + r];
+        sl.cap[r] = rank_capacity[first + r];
+        if (shards) {
+            sl.shard[r] = shards[first + r];
+            sl.numel[r] = plan->rank_numel[first + r];
+        }
+    }
+    return sl;
+}
+
+bool buckets_ok(const dte_plan* plan, int64_t* const* out_off, uint16_t* const* out_val,
+                const int64_t* rank_capacity)
+{
+    for (int32_t r = 0; r < plan->nranks; ++r) {
+        if (rank_capacity[r] < 0) return false;
+        if (rank_capacity[r] > 0 && (!out_off[r] || !out_val[r])) return false;
+    }
+    return true;
+}
+
+bool shards_ok(const dte_plan* plan, uint16_t* const* shards)
+{
+    if (!shards) return false;
+    for (int32_t r = 0; r < plan->nranks; ++r)
+        if (plan->rank_numel[r] > 0 && !shards[r]) return false;
+    return true;
+}
+
+bool remap_args_ok(const dte_plan* plan, const int64_t* idx, const uint16_t* val,
+                   const int64_t* count, int64_t in_capacity, int64_t* const* out_off,
+                   uint16_t* const* out_val, const int64_t* rank_capacity,
+                   const int64_t* rank_count)
+{
+    if (!plan || !count || !out_off || !out_val || !rank_capacity || !rank_count ||
+        in_capacity < 0 || !on_plan_device(plan))
+        return false;
+    if (in_capacity > 0 && (!idx || !val)) return false;
+    return buckets_ok(plan, out_off, out_val, rank_capacity);
+}
+
+dte_status remap_slices(const dte_plan* plan, const int64_t* idx, const uint16_t* val,
+                        const int64_t* count, int64_t in_capacity, int64_t* const* out_off,
+                        uint16_t* const* out_val, const int64_t* rank_capacity,
+                        int64_t* rank_count, uint16_t* const* shards, hipStream_t s)
+{
+    const int cus = cu_count(plan->device);
+    for (int32_t first = 0; first < plan->nranks; first += dte::kRanksPerLaunch) {
+        const dte::RankSlice sl =
+            rank_slice(plan, first, out_off, out_val, rank_capacity, shards);
+        if (dte::launch_remap(plan->view, idx, val, count, in_capacity, sl, rank_count, cus, s) !=
+            hipSuccess)
+            return DTE_ERR_HIP;
+    }
+    return DTE_OK;
+}
+
+dte_status extract_remap(const float* p, const float* m, const float* v, int64_t n,
+                         int64_t index_base, const dte_adamw_step* hp, const dte_plan* plan,
+                         int64_t* const* out_off, uint16_t* const* out_val,
+                         const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
+                         uint16_t* const* shards, hipStream_t s)
+{
+    if (!plan || !out_off || !out_val || !rank_capacity || !rank_count ||
+        plan->nranks > dte::kRanksPerLaunch || !on_plan_device(plan))
+        return DTE_ERR_ARG;
+    if (!extract_args_ok(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count))
+        return DTE_ERR_ARG;
+    if (!buckets_ok(plan, out_off, out_val, rank_capacity)) return DTE_ERR_ARG;
+    if (n == 0) return DTE_OK;
+    dte::ExtractParams a = extract_params(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count,
+                                          nullptr);
+    a.route = 1;
+    a.plan = plan->view;
+    a.out = rank_slice(plan, 0, out_off, out_val, rank_capacity, shards);
+    a.rank_count = rank_count;
+    return dte::launch_extract(a, cu_count(plan->device), s) == hipSuccess ? DTE_OK : DTE_ERR_HIP;
+}
+
+}  // namespace
+
 extern "C" {
 
 dte_status dte_plan_create(const dte_segment* segs, int32_t nseg, const dte_op* ops,
@@ -719,32 +813,26 @@ dte_status dte_remap(const dte_plan* plan, const int64_t* idx, const uint16_t* v
                      uint16_t* const* out_val, const int64_t* rank_capacity,
                      int64_t* rank_count, void* stream)
 {
-    if (!plan || !count || !out_off || !out_val || !rank_capacity || !rank_count ||
-        in_capacity < 0 || !on_plan_device(plan))
+    if (!remap_args_ok(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacity,
+                       rank_count))
         return DTE_ERR_ARG;
-    if (in_capacity > 0 && (!idx || !val)) return DTE_ERR_ARG;
-    for (int32_t r = 0; r < plan->nranks; ++r) {
-        if (rank_capacity[r] < 0) return DTE_ERR_ARG;
-        if (rank_capacity[r] > 0 && (!out_off[r] || !out_val[r])) return DTE_ERR_ARG;
-    }
     hipStream_t s = (hipStream_t)stream;
     if (dte::launch_zero_i64(rank_count, plan->nranks, s) != hipSuccess) return DTE_ERR_HIP;
-    const int cus = cu_count(plan->device);
-    for (int32_t first = 0; first < plan->nranks; first += dte::kRanksPerLaunch) {
-        dte::RankSlice sl;
-        std::memset(&sl, 0, sizeof sl);
-        sl.first = first;
-        sl.count = std::min<int32_t>(dte::kRanksPerLaunch, plan->nranks - first);
-        for (int32_t r = 0; r < sl.count; ++r) {
-            sl.off[r] = out_off[first + r];
-            sl.val[r] = out_val[first + r];
-            sl.cap[r] = rank_capacity[first + r];
-        }
-        if (dte::launch_remap(plan->view, idx, val, count, in_capacity, sl, rank_count, cus, s) !=
-            hipSuccess)
-            return DTE_ERR_HIP;
-    }
-    return DTE_OK;
+    return remap_slices(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacity,
+                        rank_count, nullptr, s);
+}
+
+dte_status dte_remap_apply(const dte_plan* plan, const int64_t* idx, const uint16_t* val,
+                           const int64_t* count, int64_t in_capacity, int64_t* const* out_off,
+                           uint16_t* const* out_val, const int64_t* rank_capacity,
+                           int64_t* rank_count, uint16_t* const* shards, void* stream)
+{
+    if (!remap_args_ok(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacity,
+                       rank_count) ||
+        !shards_ok(plan, shards))
+        return DTE_ERR_ARG;
+    return remap_slices(plan, idx, val, count, in_capacity, out_off, out_val, rank_capacity,
+                        rank_count, shards, (hipStream_t)stream);
 }
 
 dte_status dte_extract_remap(const float* p, const float* m, const float* v, int64_t n,
@@ -753,32 +841,20 @@ dte_status dte_extract_remap(const float* p, const float* m, const float* v, int
                              const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
                              void* stream)
 {
-    if (!plan || !out_off || !out_val || !rank_capacity || !rank_count ||
-        plan->nranks > dte::kRanksPerLaunch || !on_plan_device(plan))
-        return DTE_ERR_ARG;
-    if (!extract_args_ok(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count))
-        return DTE_ERR_ARG;
-    for (int32_t r = 0; r < plan->nranks; ++r) {
-        if (rank_capacity[r] < 0) return DTE_ERR_ARG;
-        if (rank_capacity[r] > 0 && (!out_off[r] || !out_val[r])) return DTE_ERR_ARG;
-    }
-    if (n == 0) return DTE_OK;
-    dte::ExtractParams a = extract_params(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count,
-                                          nullptr);
-    a.route = 1;
-    a.plan = plan->view;
-    std::memset(&a.out, 0, sizeof a.out);
-    a.out.first = 0;
-    a.out.count = plan->nranks;
-    for (int32_t r = 0; r < plan->nranks; ++r) {
-        a.out.off[r] = out_off[r];
-        a.out.val[r] = out_val[r];
-        a.out.cap[r] = rank_capacity[r];
-    }
-    a.rank_count = rank_count;
-    return dte::launch_extract(a, cu_count(plan->device), (hipStream_t)stream) == hipSuccess
-               ? DTE_OK
-               : DTE_ERR_HIP;
+    return extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
+                         rank_count, count, nullptr, (hipStream_t)stream);
+}
+
+dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v, int64_t n,
+                                   int64_t index_base, const dte_adamw_step* hp,
+                                   const dte_plan* plan, int64_t* const* out_off,
+                                   uint16_t* const* out_val, const int64_t* rank_capacity,
+                                   int64_t* rank_count, int64_t* count, uint16_t* const* shards,
+                                   void* stream)
+{
+    if (!plan || !shards_ok(plan, shards)) return DTE_ERR_ARG;
+    return extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
+                         rank_count, count, shards, (hipStream_t)stream);
 }
 
 dte_status dte_apply(const dte_plan* plan, uint16_t* const* shards, const int64_t* const* off,

@@ -42,6 +42,10 @@ struct RankSlice {                 // ranks [first, first + count) of one launch
     int64_t* off[kRanksPerLaunch];
     uint16_t* val[kRanksPerLaunch];
     int64_t cap[kRanksPerLaunch];
+    // receiver shards that take each written entry's value at its offset as
+    // well (numel 0: none)
+    uint16_t* shard[kRanksPerLaunch];
+    int64_t numel[kRanksPerLaunch];
 };
 
 // ---- extract (fused AdamW inverse + BF16 detection + compaction) --------

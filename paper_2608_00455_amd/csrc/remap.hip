@@ -74,8 +74,6 @@ __device__ __forceinline__ void route_chunk(const PlanView& pl, const RankSlice&
         const int r = o.rank - out.first;
         if (r < 0 || r >= out.count) continue;
         int run = __builtin_amdgcn_readlane(runv, r);
-        int64_t* const off = out.off[r];
-        uint16_t* const val = out.val[r];
         const int64_t cap = out.cap[r];
         const int64_t base = kWrite ? readlane64(basev, r) : 0;
 #pragma unroll
@@ -84,10 +82,7 @@ __device__ __forceinline__ void route_chunk(const PlanView& pl, const RankSlice&
             const uint64_t b = __ballot(in);
             if (kWrite && in) {
                 const int64_t pos = base + run + lane_prefix(b);
-                if (pos < cap) {
-                    off[pos] = ravel<kNd>(o, u[j]);
-                    val[pos] = y[j];
-                }
+                if (pos < cap) emit(out, r, pos, ravel<kNd>(o, u[j]), y[j]);
             }
             run += __popcll(b);
         }

@@ -100,6 +100,15 @@ __device__ __forceinline__ DevOp load_op(const DevOp* ops, int32_t k)
     return o;
 }
 
+// One routed entry: to position pos of rank r's bucket and, where the call
+// applies as well, to the rank's shard at once.  r is wave-uniform.
+__device__ __forceinline__ void emit(const RankSlice& out, int r, int64_t pos, int64_t j, uint16_t v)
+{
+    out.off[r][pos] = j;
+    out.val[r][pos] = v;
+    if ((uint64_t)j < (uint64_t)out.numel[r]) __builtin_nontemporal_store(v, out.shard[r] + j);
+}
+
 // Unravel a segment-local offset over a row-major shape of nd dimensions
 // (eq. canonical_unravel); kNd as for `inside` (kNd == 0: nd).
 template <int kNd>
@@ -158,14 +167,8 @@ __device__ __forceinline__ void route_slot(const PlanView& pl, const RankSlice& 
             const int start = __builtin_amdgcn_readlane(runv, r);
             if (lane == r) runv += __popcll(b);
             if (kWrite) {
-                int64_t* const off = out.off[r];
-                uint16_t* const val = out.val[r];
-                const int64_t cap = out.cap[r];
                 const int64_t pos = readlane64(basev, r) + start + lane_prefix(b);
-                if (in && pos < cap) {
-                    off[pos] = ravel<0>(o, u);
-                    val[pos] = v;
-                }
+                if (in && pos < out.cap[r]) emit(out, r, pos, ravel<0>(o, u), v);
             }
         }
     }

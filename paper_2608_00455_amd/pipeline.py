@@ -72,12 +72,15 @@ class DeltaPipeline:
         self.rank_capacity = [int(x) for x in rc]
         self.idx = torch.empty(max(1, self.capacity), dtype=torch.int64, device=self.device)
         self.val = torch.empty(max(1, self.capacity), dtype=torch.int16, device=self.device)
-        self.cursor = torch.zeros(1, dtype=torch.int64, device=self.device)
+        # the cursor and the rank counts side by side (a cache line apart), so
+        # that a step clears both with one fill
+        self._counters = torch.zeros(16 + R, dtype=torch.int64, device=self.device)
+        self.cursor = self._cursor = self._counters[:1]
         self.off = [torch.empty(max(1, c), dtype=torch.int64, device=self.device)
                     for c in self.rank_capacity]
         self.rval = [torch.empty(max(1, c), dtype=torch.int16, device=self.device)
                      for c in self.rank_capacity]
-        self.rank_count = torch.zeros(R, dtype=torch.int64, device=self.device)
+        self.rank_count = self._rank_count = self._counters[16:]
         if shards is None:
             shards = [torch.zeros(max(1, n), dtype=torch.int16, device=self.device)
                       for n in spec.rank_numel]
@@ -142,6 +145,32 @@ class DeltaPipeline:
                          out_prev=out_prev[b:e] if out_prev is not None else None,
                          stream=stream)
 
+    def _reset_counters(self, stream=None):
+        """Cursor and rank counts = 0 (one fill while both are the
+        pipeline's own)."""
+        with torch.cuda.stream(stream) if stream is not None else _null():
+            if self.cursor is self._cursor and self.rank_count is self._rank_count:
+                self._counters.zero_()
+            else:
+                self.cursor.zero_()
+                self.rank_count.zero_()
+
+    def _remap_apply(self, stream=None):
+        """remap and apply in one kernel; rank counts cleared before."""
+        B.dte_remap_apply(self.plan.handle, self.idx.data_ptr(), self.val.data_ptr(),
+                          self.cursor.data_ptr(), self.capacity,
+                          [t.data_ptr() for t in self.off], [t.data_ptr() for t in self.rval],
+                          self.rank_capacity, self.rank_count.data_ptr(),
+                          [t.data_ptr() for t in self.shards], _stream(stream))
+
+    def _extract_remap_apply(self, p, m, v, hp, n=None, index_base=0, stream=None):
+        n = self._check_state(p, m, v, n)
+        B.dte_extract_remap_apply(p.data_ptr(), m.data_ptr(), v.data_ptr(), n, index_base, hp,
+                                  self.plan.handle, [t.data_ptr() for t in self.off],
+                                  [t.data_ptr() for t in self.rval], self.rank_capacity,
+                                  self.rank_count.data_ptr(), self.cursor.data_ptr(),
+                                  [t.data_ptr() for t in self.shards], _stream(stream))
+
     def extract_remap(self, p, m, v, hp, n=None, index_base=0, stream=None):
         """Changed entries routed straight into the buckets (adds to
         rank_count and to the cursor; clear both first, see step_fused)."""
@@ -152,28 +181,24 @@ class DeltaPipeline:
                             self.rank_count.data_ptr(), self.cursor.data_ptr(), _stream(stream))
 
     def step_fused(self, p, m, v, hp, stream=None, runs=None):
-        """The step with detection and remap in one kernel, then apply."""
-        with torch.cuda.stream(stream) if stream is not None else _null():
-            self.cursor.zero_()
-            self.rank_count.zero_()
+        """The step with detection, remap and apply in one kernel."""
+        self._reset_counters(stream)
         if runs is None:
-            self.extract_remap(p, m, v, hp, stream=stream)
+            self._extract_remap_apply(p, m, v, hp, stream=stream)
         else:
             for b, e, h in runs:
-                self.extract_remap(p[b:e], m[b:e], v[b:e], h, n=e - b, index_base=b,
-                                   stream=stream)
-        self.apply(stream)
+                self._extract_remap_apply(p[b:e], m[b:e], v[b:e], h, n=e - b, index_base=b,
+                                          stream=stream)
 
     def step(self, p, m, v, hp, stream=None, runs=None):
-        """reset, extract (over `runs` when the shard has several parameter
-        groups), remap, apply."""
-        self.reset(stream)
+        """Fresh counters, extract (over `runs` when the shard has several
+        parameter groups), remap and apply."""
+        self._reset_counters(stream)
         if runs is None:
             self.extract(p, m, v, hp, stream=stream)
         else:
             self.extract_runs(p, m, v, runs, stream=stream)
-        self.remap(stream)
-        self.apply(stream)
+        self._remap_apply(stream)
 
     # -- host read-back (tests) --------------------------------------------
     def delta(self, raw=False):

@@ -85,6 +85,10 @@ def test_argument_errors_and_empty_calls():
     assert B.raw_status("dte_plan_info", None, None, None, None) == B.DTE_ERR_ARG
     assert B.raw_status("dte_remap", None, 16, 16, 16, 4, None, None, None, 16,
                         None) == B.DTE_ERR_ARG
+    assert B.raw_status("dte_remap_apply", None, 16, 16, 16, 4, None, None, None, 16, None,
+                        None) == B.DTE_ERR_ARG
+    assert B.raw_status("dte_extract_remap_apply", 16, 16, 16, 4, 0, ctypes.byref(hp), None, None,
+                        None, None, 16, 16, None, None) == B.DTE_ERR_ARG
     assert B.raw_status("dte_apply", None, None, None, None, 16, None, None) == B.DTE_ERR_ARG
     B.dte_plan_destroy(None)
     assert "ERR_PLAN" in B.dte_status_string(B.DTE_ERR_PLAN)
