@@ -166,6 +166,28 @@ dte_status dte_extract_delta_ordered(const float* p, const float* m, const float
                                      int64_t* cursor, void* workspace, int64_t workspace_bytes,
                                      float* out_prev, void* stream);
 
+/* Elements [begin, end) of the flat trainer shard and the step that made
+ * them (one parameter group, paper sec. 4.1). */
+typedef struct {
+    int64_t begin;
+    int64_t end;
+    dte_adamw_step hp;
+} dte_run;
+
+/* dte_extract_delta of each run in turn, appended to one delta; adjoining
+ * runs share launches.  p, m, v (and out_prev, or NULL) point to element 0
+ * of the shard, runs (host) hold absolute offsets, which are also the
+ * entries' offsets.  With a workspace (as for dte_extract_delta_ordered)
+ * each run's entries are ascending and follow those of the runs before it;
+ * with workspace NULL their order is unspecified.  Errors: DTE_ERR_ARG
+ * (before any work: nruns < 0, begin < 0, end < begin, an invalid hp, a null
+ * pointer with a run that is not empty, a small or misaligned workspace),
+ * DTE_ERR_HIP. */
+dte_status dte_extract_runs(const float* p, const float* m, const float* v, const dte_run* runs,
+                            int32_t nruns, int64_t* out_idx, uint16_t* out_val, int64_t capacity,
+                            int64_t* cursor, void* workspace, int64_t workspace_bytes,
+                            float* out_prev, void* stream);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * ordered call of dte_extract_delta_ordered with its workspace in a static
@@ -312,15 +334,15 @@ dte_status dte_extract_remap(const float* p, const float* m, const float* v, int
                              const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
                              void* stream);
 
-/* dte_extract_remap that also stores every entry that reaches a bucket to
- * its receiver's shard (dte_apply of the call's own entries).  Arguments and
- * errors as in dte_extract_remap and dte_apply. */
-dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v, int64_t n,
-                                   int64_t index_base, const dte_adamw_step* hp,
-                                   const dte_plan* plan, int64_t* const* out_off,
-                                   uint16_t* const* out_val, const int64_t* rank_capacity,
-                                   int64_t* rank_count, int64_t* count, uint16_t* const* shards,
-                                   void* stream);
+/* dte_extract_remap over several runs (as in dte_extract_runs) that also
+ * stores every entry that reaches a bucket to its receiver's shard
+ * (dte_apply of the call's own entries).  Other arguments and errors as in
+ * dte_extract_remap and dte_apply. */
+dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v,
+                                   const dte_run* runs, int32_t nruns, const dte_plan* plan,
+                                   int64_t* const* out_off, uint16_t* const* out_val,
+                                   const int64_t* rank_capacity, int64_t* rank_count,
+                                   int64_t* count, uint16_t* const* shards, void* stream);
 
 /* Direct sparse apply (paper sec. 4.3, eq. direct_sparse_apply):
  * shards[r][off[r][k]] = val[r][k] for k < min(rank_count[r],

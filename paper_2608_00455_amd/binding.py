@@ -20,7 +20,7 @@ EXPORTED = ("dte_derive_scalars", "dte_extract_delta", "dte_ordered_workspace_by
             "dte_extract_delta_ordered", "dte_extract_delta_ordered_noalloc",
             "dte_ordered_noalloc_max_capacity", "dte_plan_create", "dte_plan_destroy",
             "dte_plan_info", "dte_remap", "dte_extract_remap", "dte_apply", "dte_remap_apply",
-            "dte_extract_remap_apply", "dte_adamw_forward", "dte_status_string")
+            "dte_extract_remap_apply", "dte_extract_runs", "dte_adamw_forward", "dte_status_string")
 
 
 class DteError(RuntimeError):
@@ -37,6 +37,10 @@ class dte_adamw_step(ctypes.Structure):
                 ("beta2", ctypes.c_double), ("eps", ctypes.c_double),
                 ("weight_decay", ctypes.c_double), ("step", ctypes.c_int64),
                 ("order", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+class dte_run(ctypes.Structure):
+    _fields_ = [("begin", ctypes.c_int64), ("end", ctypes.c_int64), ("hp", dte_adamw_step)]
 
 
 class dte_scalars(ctypes.Structure):
@@ -108,8 +112,12 @@ def _lib():
         L.dte_remap_apply.restype = S
         L.dte_remap_apply.argtypes = L.dte_remap.argtypes[:-1] + [ctypes.POINTER(P), P]
         L.dte_extract_remap_apply.restype = S
-        L.dte_extract_remap_apply.argtypes = (L.dte_extract_remap.argtypes[:-1] +
-                                              [ctypes.POINTER(P), P])
+        L.dte_extract_remap_apply.argtypes = [P, P, P, ctypes.POINTER(dte_run), I32, P,
+                                              ctypes.POINTER(P), ctypes.POINTER(P),
+                                              ctypes.POINTER(I64), P, P, ctypes.POINTER(P), P]
+        L.dte_extract_runs.restype = S
+        L.dte_extract_runs.argtypes = [P, P, P, ctypes.POINTER(dte_run), I32, P, P, I64, P, P,
+                                       I64, P, P]
         L.dte_apply.restype = S
         L.dte_apply.argtypes = [P, ctypes.POINTER(P), ctypes.POINTER(P), ctypes.POINTER(P), P,
                                 ctypes.POINTER(I64), P]
@@ -191,12 +199,25 @@ def dte_extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_c
                                     rank_count, count, stream or None))
 
 
-def dte_extract_remap_apply(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
-                            rank_count, count, shards, stream=0):
+def _runs(runs):
+    return (dte_run * max(1, len(runs)))(*[dte_run(b, e, _hp(h)) for b, e, h in runs])
+
+
+def dte_extract_runs(p, m, v, runs, out_idx, out_val, capacity, cursor, workspace=0,
+                     workspace_bytes=0, out_prev=0, stream=0):
+    """runs: sequence of (begin, end, hyperparameters)."""
+    _check("dte_extract_runs",
+           _lib().dte_extract_runs(p, m, v, _runs(runs), len(runs), out_idx, out_val, capacity,
+                                   cursor, workspace or None, workspace_bytes, out_prev or None,
+                                   stream or None))
+
+
+def dte_extract_remap_apply(p, m, v, runs, plan, out_off, out_val, rank_capacity, rank_count,
+                            count, shards, stream=0):
     _check("dte_extract_remap_apply",
-           _lib().dte_extract_remap_apply(p, m, v, n, index_base, ctypes.byref(_hp(hp)), plan,
-                                          _ptrs(out_off), _ptrs(out_val), _i64s(rank_capacity),
-                                          rank_count, count, _ptrs(shards), stream or None))
+           _lib().dte_extract_remap_apply(p, m, v, _runs(runs), len(runs), plan, _ptrs(out_off),
+                                          _ptrs(out_val), _i64s(rank_capacity), rank_count, count,
+                                          _ptrs(shards), stream or None))
 
 
 def dte_adamw_forward(p, m, v, g, n, hp, stream=0):

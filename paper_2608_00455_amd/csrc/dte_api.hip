@@ -314,6 +314,31 @@ bool extract_args_ok(const float* p, const float* m, const float* v, int64_t n,
     return true;
 }
 
+dte::StepScalars step_scalars(const AllScalars& sc)
+{
+    dte::StepScalars k;
+    k.lrb1 = sc.s.lrb1;
+    k.rbc2 = sc.s.rbc2;
+    k.eps = sc.s.eps;
+    k.decay = sc.s.decay;
+    // one binary32 step below and above the binary64 reciprocal: a
+    // bracket of 1/decay whatever the binary64 rounding did
+    const float r = (float)(1.0 / (double)sc.s.decay);
+    const bool grows = sc.s.decay < 1.0f;     // 1/decay > 1
+    k.rd = std::nextafter(r, grows ? INFINITY : 0.0f);
+    k.far = grows ? 0xFFFFFFFFu : 0u;
+    k.lr = sc.s.lr;
+    k.bc1 = sc.s.bc1;
+    k.bc2 = sc.s.bc2;
+    // literal order: the "unchanged" proof holds only for these scalars
+    // (extract.hip, proven_unchanged)
+    k.lit_filter = k.eps >= 0x1p-40f && k.lr <= 0x1p20f && k.bc1 >= 0x1p-20f && k.bc2 >= 0x1p-20f;
+    k.floor = k.lit_filter
+                  ? std::nextafter((float)(0x1p-124 / std::min(1.0, (double)k.eps)), INFINITY)
+                  : 0x1p-126f;
+    return k;
+}
+
 dte::ExtractParams extract_params(const float* p, const float* m, const float* v, int64_t n,
                                   int64_t index_base, const dte_adamw_step* hp,
                                   int64_t* out_idx, uint16_t* out_val, int64_t capacity,
@@ -326,28 +351,9 @@ dte::ExtractParams extract_params(const float* p, const float* m, const float* v
     a.v = v;
     a.n = n;
     a.index_base = index_base;
-    a.lrb1 = sc.s.lrb1;
-    a.rbc2 = sc.s.rbc2;
-    a.eps = sc.s.eps;
-    a.decay = sc.s.decay;
-    {
-        // one binary32 step below and above the binary64 reciprocal: a
-        // bracket of 1/decay whatever the binary64 rounding did
-        const float r = (float)(1.0 / (double)sc.s.decay);
-        const bool grows = sc.s.decay < 1.0f;     // 1/decay > 1
-        a.rd = std::nextafter(r, grows ? INFINITY : 0.0f);
-        a.far = grows ? 0xFFFFFFFFu : 0u;
-    }
     a.literal = sc.s.order == DTE_ORDER_LITERAL;
-    a.lr = sc.s.lr;
-    a.bc1 = sc.s.bc1;
-    a.bc2 = sc.s.bc2;
-    // literal order: the "unchanged" proof holds only for these scalars
-    // (extract.hip, proven_unchanged)
-    a.lit_filter = a.eps >= 0x1p-40f && a.lr <= 0x1p20f && a.bc1 >= 0x1p-20f && a.bc2 >= 0x1p-20f;
-    a.floor = a.lit_filter
-                  ? std::nextafter((float)(0x1p-124 / std::min(1.0, (double)a.eps)), INFINITY)
-                  : 0x1p-126f;
+    a.step = step_scalars(sc);
+    a.nruns = 1;
     a.out_idx = out_idx;
     a.out_val = out_val;
     a.capacity = capacity;
@@ -356,6 +362,63 @@ dte::ExtractParams extract_params(const float* p, const float* m, const float* v
     a.runs = nullptr;
     a.route = 0;
     return a;
+}
+
+bool runs_ok(const dte_run* runs, int32_t nruns, bool* any)
+{
+    if (nruns < 0 || (nruns > 0 && !runs)) return false;
+    for (int32_t k = 0; k < nruns; ++k) {
+        if (runs[k].begin < 0 || runs[k].end < runs[k].begin || !valid_hp(&runs[k].hp) ||
+            !bias_ok(runs[k].hp))
+            return false;
+        *any = *any || runs[k].end > runs[k].begin;
+    }
+    return true;
+}
+
+// Calls launch for each group of consecutive, adjoining runs that one launch
+// can take (one operation order, kRunsPerLaunch runs of different scalars).
+// `common`: the state's first element, theta_hat's, and the outputs.
+extern "C++" template <typename Launch>
+dte_status launch_runs(const dte::ExtractParams& common, const dte_run* runs, int32_t nruns,
+                       const Launch& launch)
+{
+    for (int32_t k = 0; k < nruns;) {
+        int64_t end = 0, last = 0;
+        dte::ExtractParams a = common;
+        a.nruns = 0;
+        for (; k < nruns; ++k) {
+            if (runs[k].end == runs[k].begin) continue;
+            const AllScalars sc = derive(runs[k].hp);
+            const int32_t literal = sc.s.order == DTE_ORDER_LITERAL;
+            if (a.nruns > 0 && (runs[k].begin != end || literal != a.literal ||
+                                last >= dte::kRunElements ||
+                                runs[k].end - runs[k].begin >= dte::kRunElements))
+                break;
+            const dte::StepScalars step = step_scalars(sc);
+            if (a.nruns == 0 || std::memcmp(&step, &a.table.step[a.nruns - 1], sizeof step) != 0) {
+                if (a.nruns == dte::kRunsPerLaunch) break;
+                if (a.nruns == 0) {
+                    a.p += runs[k].begin;
+                    a.m += runs[k].begin;
+                    a.v += runs[k].begin;
+                    if (a.out_prev) a.out_prev += runs[k].begin;
+                    a.index_base = runs[k].begin;
+                    a.literal = literal;
+                    a.step = step;
+                }
+                a.table.step[a.nruns++] = step;
+            }
+            end = runs[k].end;
+            last = end - runs[k].begin;
+            a.n = end - a.index_base;
+            a.table.end[a.nruns - 1] = a.n;
+        }
+        if (a.nruns == 0) continue;
+        const dte_status st = launch(a);
+        if (st != DTE_OK) return st;
+    }
+    return DTE_OK;
 }
 
 // Ordered-mode workspace: per-wave regions (capacity entries in all), the
@@ -418,23 +481,24 @@ int64_t dte_ordered_workspace_bytes(int64_t capacity)
 
 namespace {
 
-// The ordered call on a workspace of workspace_bytes at `workspace`
-// (device, 256-byte aligned, at least dte_ordered_workspace_bytes(capacity)).
-dte_status extract_ordered(const float* p, const float* m, const float* v, int64_t n,
-                           int64_t index_base, const dte_adamw_step* hp, int64_t* out_idx,
-                           uint16_t* out_val, int64_t capacity, int64_t* cursor, void* workspace,
-                           float* out_prev, hipStream_t s)
+// The ordered call of `a` (as for the unordered one) on a workspace (device,
+// 256-byte aligned, at least dte_ordered_workspace_bytes(a.capacity)).
+dte_status extract_ordered(dte::ExtractParams a, void* workspace, hipStream_t s)
 {
-    const OrderedWorkspace w = ordered_layout(capacity);
+    const OrderedWorkspace w = ordered_layout(a.capacity);
     char* base = static_cast<char*>(workspace);
     int64_t* counters = reinterpret_cast<int64_t*>(base + w.counters);
     const int cus = current_cus();
     // unordered fill level and run count start at zero (a fill kernel)
     if (dte::launch_zero_i64(counters, 2, s) != hipSuccess) return DTE_ERR_HIP;
-    dte::ExtractParams a = extract_params(p, m, v, n, index_base, hp,
-                                          reinterpret_cast<int64_t*>(base + w.idx),
-                                          reinterpret_cast<uint16_t*>(base + w.val), capacity,
-                                          counters, out_prev);
+    dte::OrderParams o;
+    o.out_idx = a.out_idx;
+    o.out_val = a.out_val;
+    o.capacity = a.capacity;
+    o.cursor = a.cursor;
+    a.out_idx = reinterpret_cast<int64_t*>(base + w.idx);
+    a.out_val = reinterpret_cast<uint16_t*>(base + w.val);
+    a.cursor = counters;
     a.runs = reinterpret_cast<dte::OrderRun*>(base + w.runs);
     a.max_runs = w.max_runs;
     a.run_cursor = counters + 1;
@@ -442,10 +506,9 @@ dte_status extract_ordered(const float* p, const float* m, const float* v, int64
     a.region_idx = reinterpret_cast<int64_t*>(base + w.ridx);
     a.region_val = reinterpret_cast<uint16_t*>(base + w.rval);
     a.region_count = reinterpret_cast<int64_t*>(base + w.region_count);
-    const int64_t waves = dte::extract_waves(n, cus);
-    a.region_size = capacity / waves;
+    const int64_t waves = dte::extract_waves(a.n, cus);
+    a.region_size = a.capacity / waves;
     if (dte::launch_extract(a, cus, s) != hipSuccess) return DTE_ERR_HIP;
-    dte::OrderParams o;
     o.runs = a.runs;
     o.run_cursor = a.run_cursor;
     o.max_runs = w.max_runs;
@@ -454,19 +517,46 @@ dte_status extract_ordered(const float* p, const float* m, const float* v, int64
     o.waves = (int32_t)waves;
     o.src_idx = a.out_idx;
     o.src_val = a.out_val;
-    o.src_capacity = capacity;
+    o.src_capacity = a.capacity;
     o.region_idx = a.region_idx;
     o.region_val = a.region_val;
     o.region_count = a.region_count;
     o.region_size = a.region_size;
-    o.out_idx = out_idx;
-    o.out_val = out_val;
-    o.capacity = capacity;
-    o.cursor = cursor;
     return dte::launch_order(o, cus, s) == hipSuccess ? DTE_OK : DTE_ERR_HIP;
 }
 
 }  // namespace
+
+dte_status dte_extract_runs(const float* p, const float* m, const float* v, const dte_run* runs,
+                            int32_t nruns, int64_t* out_idx, uint16_t* out_val, int64_t capacity,
+                            int64_t* cursor, void* workspace, int64_t workspace_bytes,
+                            float* out_prev, void* stream)
+{
+    bool any = false;
+    if (!runs_ok(runs, nruns, &any) || capacity < 0) return DTE_ERR_ARG;
+    if (!any) return DTE_OK;
+    if (!p || !m || !v || !cursor || (capacity > 0 && (!out_idx || !out_val))) return DTE_ERR_ARG;
+    if (workspace) {
+        const int64_t need = dte_ordered_workspace_bytes(capacity);
+        if (need < 0 || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u))
+            return DTE_ERR_ARG;
+    }
+    dte::ExtractParams a{};
+    a.p = p;
+    a.m = m;
+    a.v = v;
+    a.out_idx = out_idx;
+    a.out_val = out_val;
+    a.capacity = capacity;
+    a.cursor = cursor;
+    a.out_prev = out_prev;
+    const hipStream_t s = (hipStream_t)stream;
+    const int cus = current_cus();
+    return launch_runs(a, runs, nruns, [&](const dte::ExtractParams& b) {
+        if (workspace) return extract_ordered(b, workspace, s);
+        return dte::launch_extract(b, cus, s) == hipSuccess ? DTE_OK : DTE_ERR_HIP;
+    });
+}
 
 dte_status dte_extract_delta_ordered(const float* p, const float* m, const float* v, int64_t n,
                                      int64_t index_base, const dte_adamw_step* hp,
@@ -481,8 +571,9 @@ dte_status dte_extract_delta_ordered(const float* p, const float* m, const float
     if (need < 0 || !workspace || workspace_bytes < need ||
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return DTE_ERR_ARG;
-    return extract_ordered(p, m, v, n, index_base, hp, out_idx, out_val, capacity, cursor,
-                           workspace, out_prev, (hipStream_t)stream);
+    return extract_ordered(extract_params(p, m, v, n, index_base, hp, out_idx, out_val, capacity,
+                                          cursor, out_prev),
+                           workspace, (hipStream_t)stream);
 }
 
 // ---- the ordered call without allocation ---------------------------------
@@ -538,8 +629,9 @@ dte_status dte_extract_delta_ordered_noalloc(const float* p, const float* m, con
     if (n == 0) return DTE_OK;
     void* ws = scratch_address();
     if (ws == nullptr) return DTE_ERR_HIP;
-    return extract_ordered(p, m, v, n, index_base, hp, out_idx, out_val, capacity, cursor, ws,
-                           out_prev, (hipStream_t)stream);
+    return extract_ordered(extract_params(p, m, v, n, index_base, hp, out_idx, out_val, capacity,
+                                          cursor, out_prev),
+                           ws, (hipStream_t)stream);
 }
 
 dte_status dte_adamw_forward(float* p, float* m, float* v, const float* g, int64_t n,
@@ -755,26 +847,12 @@ dte_status remap_slices(const dte_plan* plan, const int64_t* idx, const uint16_t
     return DTE_OK;
 }
 
-dte_status extract_remap(const float* p, const float* m, const float* v, int64_t n,
-                         int64_t index_base, const dte_adamw_step* hp, const dte_plan* plan,
-                         int64_t* const* out_off, uint16_t* const* out_val,
-                         const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
-                         uint16_t* const* shards, hipStream_t s)
+bool route_args_ok(const dte_plan* plan, int64_t* const* out_off, uint16_t* const* out_val,
+                   const int64_t* rank_capacity, const int64_t* rank_count)
 {
-    if (!plan || !out_off || !out_val || !rank_capacity || !rank_count ||
-        plan->nranks > dte::kRanksPerLaunch || !on_plan_device(plan))
-        return DTE_ERR_ARG;
-    if (!extract_args_ok(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count))
-        return DTE_ERR_ARG;
-    if (!buckets_ok(plan, out_off, out_val, rank_capacity)) return DTE_ERR_ARG;
-    if (n == 0) return DTE_OK;
-    dte::ExtractParams a = extract_params(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count,
-                                          nullptr);
-    a.route = 1;
-    a.plan = plan->view;
-    a.out = rank_slice(plan, 0, out_off, out_val, rank_capacity, shards);
-    a.rank_count = rank_count;
-    return dte::launch_extract(a, cu_count(plan->device), s) == hipSuccess ? DTE_OK : DTE_ERR_HIP;
+    return plan && out_off && out_val && rank_capacity && rank_count &&
+           plan->nranks <= dte::kRanksPerLaunch && on_plan_device(plan) &&
+           buckets_ok(plan, out_off, out_val, rank_capacity);
 }
 
 }  // namespace
@@ -841,20 +919,47 @@ dte_status dte_extract_remap(const float* p, const float* m, const float* v, int
                              const int64_t* rank_capacity, int64_t* rank_count, int64_t* count,
                              void* stream)
 {
-    return extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
-                         rank_count, count, nullptr, (hipStream_t)stream);
+    if (!route_args_ok(plan, out_off, out_val, rank_capacity, rank_count) ||
+        !extract_args_ok(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count))
+        return DTE_ERR_ARG;
+    if (n == 0) return DTE_OK;
+    dte::ExtractParams a = extract_params(p, m, v, n, index_base, hp, nullptr, nullptr, 0, count,
+                                          nullptr);
+    a.route = 1;
+    a.plan = plan->view;
+    a.out = rank_slice(plan, 0, out_off, out_val, rank_capacity, nullptr);
+    a.rank_count = rank_count;
+    return dte::launch_extract(a, cu_count(plan->device), (hipStream_t)stream) == hipSuccess
+               ? DTE_OK
+               : DTE_ERR_HIP;
 }
 
-dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v, int64_t n,
-                                   int64_t index_base, const dte_adamw_step* hp,
-                                   const dte_plan* plan, int64_t* const* out_off,
-                                   uint16_t* const* out_val, const int64_t* rank_capacity,
-                                   int64_t* rank_count, int64_t* count, uint16_t* const* shards,
-                                   void* stream)
+dte_status dte_extract_remap_apply(const float* p, const float* m, const float* v,
+                                   const dte_run* runs, int32_t nruns, const dte_plan* plan,
+                                   int64_t* const* out_off, uint16_t* const* out_val,
+                                   const int64_t* rank_capacity, int64_t* rank_count,
+                                   int64_t* count, uint16_t* const* shards, void* stream)
 {
-    if (!plan || !shards_ok(plan, shards)) return DTE_ERR_ARG;
-    return extract_remap(p, m, v, n, index_base, hp, plan, out_off, out_val, rank_capacity,
-                         rank_count, count, shards, (hipStream_t)stream);
+    bool any = false;
+    if (!route_args_ok(plan, out_off, out_val, rank_capacity, rank_count) ||
+        !shards_ok(plan, shards) || !runs_ok(runs, nruns, &any))
+        return DTE_ERR_ARG;
+    if (!any) return DTE_OK;
+    if (!p || !m || !v || !count) return DTE_ERR_ARG;
+    dte::ExtractParams a{};
+    a.p = p;
+    a.m = m;
+    a.v = v;
+    a.cursor = count;
+    a.route = 1;
+    a.plan = plan->view;
+    a.out = rank_slice(plan, 0, out_off, out_val, rank_capacity, shards);
+    a.rank_count = rank_count;
+    const int cus = cu_count(plan->device);
+    return launch_runs(a, runs, nruns, [&](const dte::ExtractParams& b) {
+        return dte::launch_extract(b, cus, (hipStream_t)stream) == hipSuccess ? DTE_OK
+                                                                             : DTE_ERR_HIP;
+    });
 }
 
 dte_status dte_apply(const dte_plan* plan, uint16_t* const* shards, const int64_t* const* off,

@@ -60,20 +60,42 @@ struct OrderRun {
     int32_t wave;         // global wave number (launch order)
 };
 
-// Operation order of the step and its inverse (dte_scalars).
+// Step scalars of one run of elements (dte_scalars) and what the
+// "unchanged" proof derives from them.
+struct StepScalars {
+    float lrb1, rbc2, eps, decay;
+    float rd;             // bracket of 1/decay away from 1 (proven_unchanged), and
+    uint32_t far;         // which magnitude of p and hi it scales
+    float lr, bc1, bc2;   // literal order
+    int32_t lit_filter;   // literal order: the "unchanged" proof may be used
+    float floor;          // literal order: additive term of the proof's bound
+};
+
+// Runs of one launch that covers several parameter groups: run k < nruns
+// holds elements [end[k-1], end[k]) of the range (end[-1] = 0, end[nruns-1]
+// = n).  (The table travels as a kernel argument: 4 KB hold about 50 runs.)
+constexpr int kRunsPerLaunch = 32;
+// A run of as many elements has a launch of its own, shorter ones share: a
+// launch costs 4 to 7 us, the kernel over runs is 2 % slower than the one for
+// a single run on dense deltas, and a launch over much of the shard spreads
+// its delta over it, which apply is slower on.  Whole steps, us, every run by
+// itself -> by this rule: 13 runs of 44 M elements 260 -> 205, 16 runs of 772
+// M (42 and 151 M with vectors between them, 14 % change) 3040 -> 2918.
+constexpr int64_t kRunElements = (int64_t)1 << 24;
+struct RunTable {
+    int64_t end[kRunsPerLaunch];
+    StepScalars step[kRunsPerLaunch];
+};
+
 struct ExtractParams {
     const float* p;
     const float* m;
     const float* v;
     int64_t n;            // elements of this call
     int64_t index_base;   // flat trainer offset of element 0
-    float lrb1, rbc2, eps, decay;
-    float rd;             // bracket of 1/decay away from 1 (proven_unchanged), and
-    uint32_t far;         // which magnitude of p and hi it scales
     int32_t literal;      // order: 0 folded, 1 literal
-    float lr, bc1, bc2;   // literal order
-    int32_t lit_filter;   // literal order: the "unchanged" proof may be used
-    float floor;          // literal order: additive term of the proof's bound
+    StepScalars step;     // nruns == 1
+    int32_t nruns;        // more than one: the runs of `table`, one operation order
     int64_t* out_idx;
     uint16_t* out_val;
     int64_t capacity;
@@ -100,6 +122,7 @@ struct ExtractParams {
     PlanView plan;
     RankSlice out;
     int64_t* rank_count;
+    RunTable table;
 };
 
 // Waves that the ordered workspace's tables have room for, and the most that

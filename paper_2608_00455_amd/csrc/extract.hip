@@ -159,7 +159,7 @@ using rt::lane_prefix;   // set lanes of the mask below this lane
 // far) as unsigned patterns is the larger magnitude for far = 2^32 - 1 and
 // the smaller for far = 0.
 template <bool kDecayOne, bool kLit>
-__device__ __forceinline__ bool proven_unchanged(float p, float m, float v, const ExtractParams& a)
+__device__ __forceinline__ bool proven_unchanged(float p, float m, float v, const StepScalars& a)
 {
     const float num = a.lrb1 * m;
     float vh = v * a.rbc2;
@@ -183,7 +183,7 @@ __device__ __forceinline__ bool proven_unchanged(float p, float m, float v, cons
 
 // Exact inverse and change test of one element (sec. 4.1 / 4.2.1).
 template <bool kDecayOne, bool kLit>
-__device__ __forceinline__ float exact_prev(float p, float m, float v, const ExtractParams& a)
+__device__ __forceinline__ float exact_prev(float p, float m, float v, const StepScalars& a)
 {
     const float u = kLit ? step_term_literal(m, v, a.lr, a.bc1, a.bc2, a.eps)
                          : step_term(m, v, a.lrb1, a.rbc2, a.eps);
@@ -478,8 +478,8 @@ __device__ int block_round(const ExtractParams& a, const WaveStage& st, Staging&
 // Exact inverse of the first `count` queued candidates, 64 per pass; changed
 // ones are staged.  The rest (fewer than 64) move to the queue's front.
 template <bool kDecayOne, bool kLit, bool kRoute>
-__device__ void drain_queue(const ExtractParams& a, const WaveStage& st, int& queued, int count,
-                            Staging& so, int lane)
+__device__ void drain_queue(const ExtractParams& a, const StepScalars& k, const WaveStage& st,
+                            int& queued, int count, Staging& so, int lane)
 {
     wave_sync();
     for (int base = 0; base < count; base += 64) {
@@ -489,7 +489,7 @@ __device__ void drain_queue(const ExtractParams& a, const WaveStage& st, int& qu
         uint16_t bn = 0;
         if (i < count) {
             const f32x4 c = st.queue[i];
-            const float ph = exact_prev<kDecayOne, kLit>(c.x, c.y, c.z, a);
+            const float ph = exact_prev<kDecayOne, kLit>(c.x, c.y, c.z, k);
             bn = (uint16_t)bf16_bits(c.x);
             changed = bf16_bits(ph) != bn;
             key = __float_as_uint(c.w);
@@ -548,11 +548,12 @@ __device__ __forceinline__ void stage_slot(const WaveStage& st, int first, int f
 // One slot, at element e0 of the range.  kPrev: the exact inverse of every
 // element, theta_hat written and changed elements staged; else the elements
 // without a proof join the queue, which is drained of whole groups of 64.
-// kEdge: the slot holds elements [e0, n) only.
+// kEdge: of the slot's elements only those in [lo, hi) count.
 template <bool kEdge, bool kDecayOne, bool kPrev, bool kLit, bool kRoute>
-__device__ __forceinline__ void test_slot(const ExtractParams& a, const WaveStage& st,
-                                          Staging& so, int& queued, int lane, int64_t e0,
-                                          const f32x4& P, const f32x4& M, const f32x4& V)
+__device__ __forceinline__ void test_slot(const ExtractParams& a, const StepScalars& k,
+                                          const WaveStage& st, Staging& so, int& queued, int lane,
+                                          int64_t e0, const f32x4& P, const f32x4& M,
+                                          const f32x4& V, int64_t lo, int64_t hi)
 {
     const int64_t e = e0 + lane * 4;
     const uint32_t key = (uint32_t)(e0 - st.base) + lane * 4;
@@ -561,13 +562,13 @@ __device__ __forceinline__ void test_slot(const ExtractParams& a, const WaveStag
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         if (kPrev) {
-            prev[c] = exact_prev<kDecayOne, kLit>(P[c], M[c], V[c], a);
+            prev[c] = exact_prev<kDecayOne, kLit>(P[c], M[c], V[c], k);
             sel[c] = bf16_bits(prev[c]) != bf16_bits(P[c]);
         } else {
-            sel[c] = (kLit && !a.lit_filter) ||
-                     !proven_unchanged<kDecayOne, kLit>(P[c], M[c], V[c], a);
+            sel[c] = (kLit && !k.lit_filter) ||
+                     !proven_unchanged<kDecayOne, kLit>(P[c], M[c], V[c], k);
         }
-        if (kEdge) sel[c] = sel[c] && e + c < a.n;
+        if (kEdge) sel[c] = sel[c] && e + c >= lo && e + c < hi;
     }
     const Slot4 r = select4(sel);
     if (kPrev) {
@@ -587,7 +588,7 @@ __device__ __forceinline__ void test_slot(const ExtractParams& a, const WaveStag
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (e + c < a.n) a.out_prev[e + c] = prev[c];
+                if (e + c >= lo && e + c < hi) a.out_prev[e + c] = prev[c];
         }
     } else if (r.count != 0) {
         int pos = queued + lanes_before(r);
@@ -598,11 +599,66 @@ __device__ __forceinline__ void test_slot(const ExtractParams& a, const WaveStag
         }
         queued += r.count;
         if (queued >= kDrain)
-            drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued & ~63, so, lane);
+            drain_queue<kDecayOne, kLit, kRoute>(a, k, st, queued, queued & ~63, so, lane);
     }
 }
 
-// One launch covers the range.  kFull: n is a multiple of kSlot.
+// The run of a wave's current slot: elements [.., end) of the range and their
+// scalars (wave-uniform).  Lane k holds run k's end and scalars, so that a
+// look-up costs a ballot and a few register reads, no memory latency.
+struct CurrentRun {
+    int64_t end;
+    StepScalars step;
+    int64_t lane_end;
+    uint32_t lane_step[sizeof(StepScalars) / 4];
+};
+
+__device__ __forceinline__ void load_runs(const ExtractParams& a, CurrentRun& r, int lane)
+{
+    const int k = lane < a.nruns ? lane : a.nruns - 1;
+    r.end = 0;
+    r.lane_end = lane < a.nruns ? a.table.end[k] : INT64_MAX;
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(&a.table.step[k]);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(StepScalars) / 4); ++i) r.lane_step[i] = w[i];
+}
+
+// The run of element e < n.
+__device__ __forceinline__ void find_run(CurrentRun& r, int64_t e)
+{
+    const int k = __popcll(__ballot(r.lane_end <= e));
+    r.end = rt::readlane64(r.lane_end, k);
+    uint32_t* w = reinterpret_cast<uint32_t*>(&r.step);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(StepScalars) / 4); ++i)
+        w[i] = __builtin_amdgcn_readlane(r.lane_step[i], k);
+}
+
+// Slot [e0, end) that is not all of the current run's.  Before the run
+// changes the queue is emptied, as its candidates are evaluated with one
+// run's scalars; a wave's slots ascend, so runs are only ever left behind.
+template <bool kPrev, bool kLit, bool kRoute>
+__device__ __forceinline__ void test_slot_runs(const ExtractParams& a, CurrentRun& run,
+                                               const WaveStage& st, Staging& so, int& queued,
+                                               int lane, int64_t e0, int64_t end, const f32x4& P,
+                                               const f32x4& M, const f32x4& V)
+{
+#pragma unroll 1
+    for (int64_t lo = e0; lo < end;) {
+        if (lo >= run.end) {
+            if (queued > 0)
+                drain_queue<false, kLit, kRoute>(a, run.step, st, queued, queued, so, lane);
+            find_run(run, lo);
+        }
+        const int64_t hi = end < run.end ? end : run.end;
+        test_slot<true, false, kPrev, kLit, kRoute>(a, run.step, st, so, queued, lane, e0, P, M, V,
+                                                    lo, hi);
+        lo = hi;
+    }
+}
+
+// One launch covers the range.  kFull: n is a multiple of kSlot.  kOneGroup:
+// one set of step scalars; else the runs of a.table.
 //
 // Bound by HBM (12 bytes read an element).  A wave streams its slots through
 // a ring of kVec slots in registers: as soon as slot s is tested, the loads
@@ -640,6 +696,9 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
     Staging so{0, 0, 0, 0, 0};
     WaveStage st{s_key[wave], s_val[wave], s_queue[wave], g * per * kSlot, (int32_t)g};
     int queued = 0;
+    CurrentRun run;
+    if (!kOneGroup) load_runs(a, run, lane);
+    const StepScalars& step = kOneGroup ? a.step : run.step;
     int round = 0;                               // block_round calls so far (LDS slot parity)
     int passes = kRound, togo = kRound;          // passes between meetings, until the next
     bool in_tail = false;
@@ -652,12 +711,32 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
         const int64_t s0 = first + it * kVec;
         const int64_t rest = (last < whole ? last : whole) - s0;
         const int left = (int)(rest < 2 * kVec ? rest : 2 * kVec);   // whole slots from s0
+        // a pass whose slots are not all of one run is tested by a loop of
+        // its own: copies of the test in the stream below made the code of a
+        // pass longer and dense ranges 1 to 2 % slower
+        const int here = it < 0 ? 0 : left < kVec ? left : kVec;
+        const bool split = !kOneGroup && here > 0 && (s0 + here) * kSlot > run.end;
+        if (split) {
+#pragma unroll 1
+            for (int j = 0; j < here; ++j) {
+                const int64_t e0 = (s0 + j) * kSlot;
+                f32x4 p = P[0], m = M[0], v = V[0];
+#pragma unroll
+                for (int i = 1; i < kVec; ++i) {
+                    p = j == i ? P[i] : p;
+                    m = j == i ? M[i] : m;
+                    v = j == i ? V[i] : v;
+                }
+                test_slot_runs<kWritePrev, kLit, kRoute>(a, run, st, so, queued, lane, e0,
+                                                         e0 + kSlot, p, m, v);
+            }
+        }
 #pragma unroll
         for (int j = 0; j < kVec; ++j) {
             const int64_t e0 = (s0 + j) * kSlot;
-            if (it >= 0 && j < left)
-                test_slot<false, kDecayOne, kWritePrev, kLit, kRoute>(a, st, so, queued, lane, e0,
-                                                                      P[j], M[j], V[j]);
+            if (!split && j < here)
+                test_slot<false, kDecayOne, kWritePrev, kLit, kRoute>(
+                    a, step, st, so, queued, lane, e0, P[j], M[j], V[j], 0, 0);
             load_slot(a, j + kVec < left, e0 + kVec * kSlot, lane, P[j], M[j], V[j]);
         }
         ++it;
@@ -681,14 +760,18 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
                     v[c] = a.v[e + c];
                 }
             }
-            test_slot<true, kDecayOne, kWritePrev, kLit, kRoute>(a, st, so, queued, lane,
-                                                                 whole * kSlot, p, m, v);
+            if (kOneGroup)
+                test_slot<true, kDecayOne, kWritePrev, kLit, kRoute>(
+                    a, step, st, so, queued, lane, whole * kSlot, p, m, v, INT64_MIN, a.n);
+            else
+                test_slot_runs<kWritePrev, kLit, kRoute>(a, run, st, so, queued, lane,
+                                                         whole * kSlot, a.n, p, m, v);
         }
         if (tail == 0) break;
         if (!in_tail) {
             // staged keys count from the stage's base: empty the queue and
             // the staging areas, then count from the tail's start
-            if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued, so, lane);
+            if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, step, st, queued, queued, so, lane);
             togo = passes = block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1,
                                         passes, true);
             st.base = s_last * kSlot;
@@ -715,7 +798,7 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
         iters = kRound;
         it = -1;
     }
-    if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, st, queued, queued, so, lane);
+    if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, step, st, queued, queued, so, lane);
     if (combine)
         block_round(a, st, so, lane, wave, s_cnt, s_base, (round++) & 1, passes, true);
     else if (so.staged > 0)
@@ -818,14 +901,32 @@ int64_t blocks_of(int64_t n, int cus)
     return b < cap ? b : cap;
 }
 
+template <bool L, bool R>
+void launch_runs(const ExtractParams& a, int cus, hipStream_t s)
+{
+    const dim3 grid((unsigned)blocks_of(a.n, cus)), block(64 * kWaves);
+    if (!R && a.out_prev)
+        hipLaunchKernelGGL((extract_kernel<false, false, false, true, L, false>), grid, block, 0, s,
+                           a);
+    else
+        hipLaunchKernelGGL((extract_kernel<false, false, false, false, L, R>), grid, block, 0, s,
+                           a);
+}
+
 template <bool D, bool L, bool R>
 void launch_range(const ExtractParams& a, int cus, hipStream_t s)
 {
     const dim3 grid((unsigned)blocks_of(a.n, cus));
-    if (a.n % kSlot == 0)
+    if (a.n % kSlot == 0) {
         launch_kernel<true, D, L, R>(a, grid, s);
-    else
+    } else if constexpr (R && !D) {   // the kernel over runs does the same work for one run
+        ExtractParams one = a;
+        one.table.end[0] = a.n;
+        one.table.step[0] = a.step;
+        launch_runs<L, true>(one, cus, s);
+    } else {
         launch_kernel<false, D, L, R>(a, grid, s);
+    }
 }
 
 // ---- ordered mode: runs to ascending positions ----------------------------
@@ -935,8 +1036,15 @@ int64_t extract_waves(int64_t n, int cus) { return n > 0 ? blocks_of(n, cus) * k
 hipError_t launch_extract(const ExtractParams& a, int cus, hipStream_t stream)
 {
     if (a.n <= 0) return hipSuccess;
-    const bool one = a.decay == 1.0f;
-    if (a.route) {
+    const bool one = a.step.decay == 1.0f;
+    if (a.nruns > 1) {
+        if (a.route)
+            a.literal ? launch_runs<true, true>(a, cus, stream)
+                      : launch_runs<false, true>(a, cus, stream);
+        else
+            a.literal ? launch_runs<true, false>(a, cus, stream)
+                      : launch_runs<false, false>(a, cus, stream);
+    } else if (a.route) {
         if (a.literal)
             one ? launch_range<true, true, true>(a, cus, stream)
                 : launch_range<false, true, true>(a, cus, stream);

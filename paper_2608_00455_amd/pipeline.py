@@ -138,8 +138,19 @@ class DeltaPipeline:
                     self.rank_count.data_ptr(), self.rank_capacity, _stream(stream))
 
     def extract_runs(self, p, m, v, runs, out_prev=None, stream=None):
-        """One dte_extract_delta per run (begin, end, hp) of the flat shard,
-        appending to the same delta (parameter groups, sec. 4.1)."""
+        """The delta of each run (begin, end, hp) of the flat shard, appended
+        to one delta (parameter groups, sec. 4.1)."""
+        runs = list(runs)
+        if _flat_runs(runs, p, m, v, out_prev):
+            self._check_state(p, m, v, max((e for _, e, _ in runs), default=0), out_prev)
+            ws = self.workspace if self.ordered else None
+            B.dte_extract_runs(p.data_ptr(), m.data_ptr(), v.data_ptr(), runs,
+                               self.idx.data_ptr(), self.val.data_ptr(), self.capacity,
+                               self.cursor.data_ptr(), ws.data_ptr() if ws is not None else 0,
+                               ws.numel() if ws is not None else 0,
+                               out_prev.data_ptr() if out_prev is not None else 0,
+                               _stream(stream))
+            return
         for b, e, hp in runs:
             self.extract(p[b:e], m[b:e], v[b:e], hp, n=e - b, index_base=b,
                          out_prev=out_prev[b:e] if out_prev is not None else None,
@@ -163,9 +174,8 @@ class DeltaPipeline:
                           self.rank_capacity, self.rank_count.data_ptr(),
                           [t.data_ptr() for t in self.shards], _stream(stream))
 
-    def _extract_remap_apply(self, p, m, v, hp, n=None, index_base=0, stream=None):
-        n = self._check_state(p, m, v, n)
-        B.dte_extract_remap_apply(p.data_ptr(), m.data_ptr(), v.data_ptr(), n, index_base, hp,
+    def _extract_remap_apply(self, p, m, v, runs, stream=None):
+        B.dte_extract_remap_apply(p.data_ptr(), m.data_ptr(), v.data_ptr(), runs,
                                   self.plan.handle, [t.data_ptr() for t in self.off],
                                   [t.data_ptr() for t in self.rval], self.rank_capacity,
                                   self.rank_count.data_ptr(), self.cursor.data_ptr(),
@@ -183,12 +193,18 @@ class DeltaPipeline:
     def step_fused(self, p, m, v, hp, stream=None, runs=None):
         """The step with detection, remap and apply in one kernel."""
         self._reset_counters(stream)
+        runs = list(runs) if runs is not None else None
         if runs is None:
-            self._extract_remap_apply(p, m, v, hp, stream=stream)
+            n = self._check_state(p, m, v, None)
+            self._extract_remap_apply(p, m, v, [(0, n, hp)], stream)
+        elif _flat_runs(runs, p, m, v):
+            self._check_state(p, m, v, max((e for _, e, _ in runs), default=0))
+            self._extract_remap_apply(p, m, v, runs, stream)
         else:
             for b, e, h in runs:
-                self._extract_remap_apply(p[b:e], m[b:e], v[b:e], h, n=e - b, index_base=b,
-                                          stream=stream)
+                self.extract_remap(p[b:e], m[b:e], v[b:e], h, n=e - b, index_base=b,
+                                   stream=stream)
+            self.apply(stream)
 
     def step(self, p, m, v, hp, stream=None, runs=None):
         """Fresh counters, extract (over `runs` when the shard has several
@@ -234,6 +250,14 @@ class _null:
 
     def __exit__(self, *a):
         return False
+
+
+def _flat_runs(runs, *state):
+    """Whether every run is a plain range of flat, dense tensors (else each
+    run's slices are taken, and checked, by themselves)."""
+    return all(0 <= b <= e for b, e, _ in runs) and all(
+        isinstance(t, torch.Tensor) and t.dim() == 1 and t.is_contiguous()
+        for t in state if t is not None)
 
 
 def generate_state(wl, hp=None, device="cuda"):

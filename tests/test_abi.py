@@ -87,8 +87,19 @@ def test_argument_errors_and_empty_calls():
                         None) == B.DTE_ERR_ARG
     assert B.raw_status("dte_remap_apply", None, 16, 16, 16, 4, None, None, None, 16, None,
                         None) == B.DTE_ERR_ARG
-    assert B.raw_status("dte_extract_remap_apply", 16, 16, 16, 4, 0, ctypes.byref(hp), None, None,
-                        None, None, 16, 16, None, None) == B.DTE_ERR_ARG
+    assert B.raw_status("dte_extract_remap_apply", 16, 16, 16, None, 0, None, None, None, None, 16,
+                        16, None, None) == B.DTE_ERR_ARG
+    runs = lambda *a: B.raw_status("dte_extract_runs", *a)  # noqa: E731
+    for bad in ((-1, 4), (5, 4)):
+        arr = (B.dte_run * 2)(B.dte_run(0, 4, hp), B.dte_run(*bad, hp))
+        assert runs(16, 16, 16, arr, 2, 16, 16, 4, 16, None, 0, None, None) == B.DTE_ERR_ARG
+    arr = (B.dte_run * 1)(B.dte_run(4, 8, hp))
+    assert runs(16, 16, 16, arr, -1, 16, 16, 4, 16, None, 0, None, None) == B.DTE_ERR_ARG
+    assert runs(16, 16, 16, None, 1, 16, 16, 4, 16, None, 0, None, None) == B.DTE_ERR_ARG
+    assert runs(None, 16, 16, arr, 1, 16, 16, 4, 16, None, 0, None, None) == B.DTE_ERR_ARG
+    assert runs(16, 16, 16, arr, 1, 16, 16, 4, 16, 256, 0, None, None) == B.DTE_ERR_ARG
+    arr[0].end = 4
+    assert runs(None, None, None, arr, 1, None, None, 0, None, None, 0, None, None) == B.DTE_OK
     assert B.raw_status("dte_apply", None, None, None, None, 16, None, None) == B.DTE_ERR_ARG
     B.dte_plan_destroy(None)
     assert "ERR_PLAN" in B.dte_status_string(B.DTE_ERR_PLAN)
