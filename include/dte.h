@@ -118,7 +118,7 @@ dte_status dte_derive_scalars(const dte_adamw_step* hp, dte_scalars* out);
  *
  * p, m, v : device, n binary32 each: theta_t, m_t, v_t of the range,
  *           element-aligned (paper sec. 4.1: optimizer-native slices).
- *           16-byte alignment of p, m, v (equal modulo 16) enables vector loads.
+ *           Loads are 16 bytes wide whatever the alignment.
  * index_base : flat trainer offset of p[0]; >= 0.
  * hp      : host; the step's hyperparameters (one parameter group per call;
  *           several groups = several calls on their sub-ranges).
