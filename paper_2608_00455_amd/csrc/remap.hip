@@ -74,7 +74,7 @@ __device__ __forceinline__ void route_chunk(const PlanView& pl, const RankSlice&
         const int r = o.rank - out.first;
         if (r < 0 || r >= out.count) continue;
         int run = __builtin_amdgcn_readlane(runv, r);
-        const int64_t cap = out.cap[r];
+        const Bucket dst = bucket(out, r);       // once per operation, not per slot
         const int64_t base = kWrite ? readlane64(basev, r) : 0;
 #pragma unroll
         for (int j = 0; j < kRemapSlots; ++j) {
@@ -82,7 +82,7 @@ __device__ __forceinline__ void route_chunk(const PlanView& pl, const RankSlice&
             const uint64_t b = __ballot(in);
             if (kWrite && in) {
                 const int64_t pos = base + run + lane_prefix(b);
-                if (pos < cap) emit(out, r, pos, ravel<kNd>(o, u[j]), y[j]);
+                if (pos < dst.cap) emit(dst, pos, ravel<kNd>(o, u[j]), y[j]);
             }
             run += __popcll(b);
         }

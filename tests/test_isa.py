@@ -8,7 +8,9 @@ this repository's own sources, gfx950):
 * no scratch memory (no register spills) in any kernel;
 * the hot extract kernels (full tiles, vector loads, no theta_hat output)
   fit three waves per SIMD as one 12-wave block per CU: at most 168 VGPRs
-  and the CU's 160 KB of LDS per block.
+  and the CU's 160 KB of LDS per block;
+* the remap kernel, which waits on latency, fits seven waves per SIMD: at
+  most 72 VGPRs.
 """
 import os
 import re
@@ -98,3 +100,8 @@ def test_hot_extract_kernels_fit_three_waves_per_simd(assembly):
             assert int(f["group_segment_fixed_size"]) <= 160 * 1024, name
     # decay == 1 or not, folded or literal order, with or without routing
     assert len(hot) == 8
+
+
+def test_remap_kernel_fits_seven_waves_per_simd(assembly):
+    (f,) = [f for name, f in kernels(assembly["remap.hip"]) if "remap_kernel" in name]
+    assert int(f["vgpr_count"]) <= 72 and int(f["agpr_count"]) == 0, f
