@@ -75,12 +75,12 @@ class DeltaPipeline:
         # the cursor and the rank counts side by side (a cache line apart), so
         # that a step clears both with one fill
         self._counters = torch.zeros(16 + R, dtype=torch.int64, device=self.device)
-        self.cursor = self._cursor = self._counters[:1]
+        self.cursor = self._counters[:1]
         self.off = [torch.empty(max(1, c), dtype=torch.int64, device=self.device)
                     for c in self.rank_capacity]
         self.rval = [torch.empty(max(1, c), dtype=torch.int16, device=self.device)
                      for c in self.rank_capacity]
-        self.rank_count = self._rank_count = self._counters[16:]
+        self.rank_count = self._counters[16:]
         if shards is None:
             shards = [torch.zeros(max(1, n), dtype=torch.int16, device=self.device)
                       for n in spec.rank_numel]
@@ -157,14 +157,16 @@ class DeltaPipeline:
                          stream=stream)
 
     def _reset_counters(self, stream=None):
-        """Cursor and rank counts = 0 (one fill while both are the
-        pipeline's own)."""
+        """Cursor and rank counts = 0 (one fill while both lie in the
+        pipeline's own memory; a caller may put others in their place)."""
         with torch.cuda.stream(stream) if stream is not None else _null():
-            if self.cursor is self._cursor and self.rank_count is self._rank_count:
-                self._counters.zero_()
+            own = self._counters
+            if self.cursor.data_ptr() == own.data_ptr() and \
+                    self.rank_count.data_ptr() == own.data_ptr() + 16 * own.element_size():
+                own.zero_()
             else:
                 self.cursor.zero_()
-                self.rank_count.zero_()
+                self.rank_count.view(-1)[:self.plan.nranks].zero_()
 
     def _remap_apply(self, stream=None):
         """remap and apply in one kernel; rank counts cleared before."""
