@@ -142,7 +142,7 @@ class DeltaPipeline:
         to one delta (parameter groups, sec. 4.1)."""
         runs = list(runs)
         if _flat_runs(runs, p, m, v, out_prev):
-            self._check_state(p, m, v, max((e for _, e, _ in runs), default=0), out_prev)
+            self._check_state(p, m, v, _runs_end(runs), out_prev)
             ws = self.workspace if self.ordered else None
             B.dte_extract_runs(p.data_ptr(), m.data_ptr(), v.data_ptr(), runs,
                                self.idx.data_ptr(), self.val.data_ptr(), self.capacity,
@@ -200,7 +200,7 @@ class DeltaPipeline:
             n = self._check_state(p, m, v, None)
             self._extract_remap_apply(p, m, v, [(0, n, hp)], stream)
         elif _flat_runs(runs, p, m, v):
-            self._check_state(p, m, v, max((e for _, e, _ in runs), default=0))
+            self._check_state(p, m, v, _runs_end(runs))
             self._extract_remap_apply(p, m, v, runs, stream)
         else:
             for b, e, h in runs:
@@ -255,11 +255,16 @@ class _null:
 
 
 def _flat_runs(runs, *state):
-    """Whether every run is a plain range of flat, dense tensors (else each
-    run's slices are taken, and checked, by themselves)."""
-    return all(0 <= b <= e for b, e, _ in runs) and all(
+    """Whether there are runs and every one is a plain range of flat, dense
+    tensors (else each run's slices are taken, and checked, by themselves)."""
+    return bool(runs) and all(0 <= b <= e for b, e, _ in runs) and all(
         isinstance(t, torch.Tensor) and t.dim() == 1 and t.is_contiguous()
         for t in state if t is not None)
+
+
+def _runs_end(runs):
+    """Elements that the state must hold: empty runs may lie anywhere."""
+    return max((e for b, e, _ in runs if e > b), default=0)
 
 
 def generate_state(wl, hp=None, device="cuda"):
