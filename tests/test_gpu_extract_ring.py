@@ -1,9 +1,11 @@
 """The extract kernel's stream of 256-element slots against the oracle where
 its shapes can go wrong: ranges just below, at and above whole slots, whole
-rings of eight slots and whole blocks of waves, bases at every element
-alignment, sparse deltas and ones that select every element of a slot (the
-candidate queue and the staging area at their fullest), and decay factors
-below, at and above one (the bound of theta_hat differs)."""
+rings (two slots in flight per wave), whole tiles of eight slots and whole
+blocks of waves, ranges that give every wave an odd or an even number of
+slots, bases at every element alignment, sparse deltas and ones that select
+every element of a slot (the candidate queue and the staging area at their
+fullest), and decay factors below, at and above one (the bound of theta_hat
+differs)."""
 import sys
 
 import numpy as np
@@ -16,9 +18,12 @@ from synth import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-SLOT, RING, WAVES = 256, 8 * 256, 12
-SIZES = [3, SLOT - 1, SLOT, SLOT + 1, RING - 1, RING + 5, WAVES * 4 * SLOT - 2,
-         WAVES * 4 * SLOT + 1, WAVES * RING * 5 + 3, 256 * WAVES * 9 * SLOT + 7]
+SLOT, RING, TILE, WAVES = 256, 2 * 256, 8 * 256, 12
+# up to four slots per wave blocks are added (of 256 CUs, one block each), then
+# the waves' ranges grow: 5, 6 and 9 slots each
+SIZES = [3, SLOT - 1, SLOT, SLOT + 1, RING - 1, RING, RING + 5, TILE - 1, TILE + 5,
+         WAVES * 4 * SLOT - 2, WAVES * 4 * SLOT + 1, WAVES * TILE * 5 + 3,
+         256 * WAVES * 5 * SLOT, 256 * WAVES * 5 * SLOT + 9 * SLOT + 7, 256 * WAVES * 9 * SLOT + 7]
 
 
 def say(*a):

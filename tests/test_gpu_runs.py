@@ -1,8 +1,9 @@
 """dte_extract_runs and the one-pass step over runs against the oracle, run by
 run: runs that begin and end inside a slot, several of them in one slot, one
 element long, empty, more than one launch takes, gaps between runs, changes
-of the operation order and of the decay factor (below, at and above one), in
-both output orders, with and without theta_hat."""
+of the operation order and of the decay factor (below, at and above one), runs
+in the dynamic tail and runs long enough for a launch of their own between
+short ones, in both output orders, with and without theta_hat."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,23 @@ def cuts(kind, n, rng):
         return [0, 1, 2, 2, 5, 200, 255, 256, 257, 300, 300, 301, 700, n - 1, n]
     if kind == "many":             # more runs than one launch takes
         return [0] + sorted(int(x) for x in rng.integers(1, n, 75)) + [n]
-    return [0, n // 3 | 1, n // 2, n]    # "large": two runs in the dynamic tail's range
+    if kind == "split":            # a run of 2^24 elements and more between short ones
+        return [0, 5001, 5001 + (1 << 24) + 333, n - 901, n]
+    # "tail": runs that begin in the dynamic tail (the last 1/16 of the slots):
+    # just before it, inside slots, at a chunk of 96 slots and inside one, one
+    # element long, in the partial slot at the end
+    slots = (n + 255) // 256
+    t, chunk = (slots - slots // 16) * 256, 96 * 256
+    return [0, n // 2 | 1, t - 300, t + 1000, t + chunk, t + 5 * chunk + 13, t + 5 * chunk + 14,
+            t + 9 * chunk + 256 * 40, n - 20, n]
+
+
+def size(kind):
+    if kind == "split":
+        return 5001 + (1 << 24) + 333 + 700 + 901
+    # the tail begins when the waves (12 per CU) have 32 slots each
+    waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+    return (32 * waves + 1000) * 256 + 77
 
 
 def state(n, seed):
@@ -39,12 +56,14 @@ def state(n, seed):
 
 
 @pytest.mark.parametrize("kind,n", [("slots", 5 * 12 * 1024), ("tiny", 1003), ("tiny", 40000),
-                                    ("many", 300_001), ("large", 256 * 12 * 20 * 256 + 77)])
+                                    ("many", 300_001), ("tail", None), ("split", None)])
 @pytest.mark.parametrize("orders", ["folded", "literal", "both"])
 @pytest.mark.parametrize("ordered", [False, True])
 def test_runs_against_oracle(kind, n, orders, ordered):
-    if kind == "large" and (orders == "both" or (orders == "literal" and ordered)):
-        pytest.skip("covered at the small sizes")
+    if n is None:
+        if orders == "both" or (orders == "literal" and ordered):
+            pytest.skip("covered at the small sizes")
+        n = size(kind)
     print("case: runs %s n %d %s ordered %d" % (kind, n, orders, ordered), flush=True)
     rng = np.random.default_rng(n)
     at = cuts(kind, n, rng)
@@ -85,16 +104,23 @@ def test_runs_against_oracle(kind, n, orders, ordered):
             assert np.array_equal(prev.cpu().numpy().view(np.uint32), full.view(np.uint32))
 
 
-@pytest.mark.parametrize("odd", [0, 3])
+@pytest.mark.parametrize("odd", [0, 3, "long"])
 @pytest.mark.parametrize("order", [W.ORDER_FOLDED, W.ORDER_LITERAL])
 def test_one_pass_step_over_runs(odd, order):
-    """The one-pass step over runs: the same shards and buckets as the step."""
-    wl = W.scaled_dense(layers=2, tp=2, hidden=256 + odd, embed=False, lr=1e-4)
+    """The one-pass step over runs: the same shards and buckets as the step
+    ("long": a run with a launch of its own between runs that share)."""
+    long = odd == "long"
+    print("case: one-pass runs, odd %s order %s" % (odd, order), flush=True)
+    odd = 1 if long else odd
+    shape = dict(hidden=1024, heads_q=8, heads_kv=2, head_dim=128, intermediate=2816) if long \
+        else dict(hidden=256 + odd)
+    wl = W.scaled_dense(layers=2, tp=2, embed=False, lr=1e-4, **shape)
     spec = layouts.build_spec(wl)
     n = wl.numel
     p, m, v = (torch.from_numpy(x).cuda() for x in state(n, odd))
     hps = [W.StepHP(lr=1e-4, weight_decay=w, order=order) for w in (0.01, 0.0, -0.1)]
-    at = [0, 255 + odd, 260, 300_001, n]
+    at = [0, 255 + odd, 260, 300_001, 300_001 + (1 << 24) + 333, 17_100_000, n] if long else \
+        [0, 255 + odd, 260, 300_001, n]
     runs = [(b, e, hps[k % 3]) for k, (b, e) in enumerate(zip(at, at[1:]))]
     pipes = [DeltaPipeline(spec, n) for _ in range(2)]
     pipes[0].step(p, m, v, None, runs=runs)
