@@ -202,8 +202,15 @@ constexpr int64_t kDenseRatio = 64;             // see write_staged
 // number the chunk, every reservation masks them off, and the block whose
 // grab is the last of all (each block's last grab finds no chunk) takes
 // them out again.
+// Where the line lies: the tail evens out the blocks' ends but costs each of
+// them a meeting and at least one more grab.  With the tail / without, us: 25
+// M elements (32 slots per wave) lr 1e-6 54.0 / 51.0, 1e-4 65.3 / 61.6, with
+// theta_hat 91.6 / 87.6, six runs 71.5 / 65.2; 30 M (38) 61.1 / 57.9, 73.9 /
+// 71.1, 106.9 / 103.5, 78.9 / 74.7; 40 M (51) 78.3 / 76.0, 93.2 / 94.0, 132 /
+// 139, 98.4 / 97.3; 60 M (76) 111.5 / 110.7, 136.8 / 140.3, 200 / 206, 141.7 /
+// 143.5; 110 M (140) 195 / 202, 256 / 267; 200 M (254) 350 / 363, 454 / 473.
 constexpr int64_t kTailDiv = 16;
-constexpr int64_t kTailSlots = 16 * kVec;
+constexpr int64_t kTailSlots = 48;
 constexpr int64_t kMaxTailSlots = (int64_t)1 << 23;
 constexpr int kGrabShift = 36;
 constexpr unsigned long long kCountMask = (1ull << kGrabShift) - 1;

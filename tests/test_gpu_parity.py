@@ -692,15 +692,15 @@ def test_extract_on_torch_adamw_states(order):
 @pytest.mark.parametrize("case", ["small", "below", "exact", "partial"])
 def test_unordered_tail_taken_in_chunks(case, ragged):
     """The unordered call's last slots of 256 elements (1/16 of them, once the
-    waves have 32 slots each) are taken by blocks, 96 slots at a time, from a
+    waves have 48 slots each) are taken by blocks, 96 slots at a time, from a
     counter in the cursor's high bits: just below that size (no tail), at it
     (whole chunks), above it with a partial last chunk, each with a whole and
     a partial last slot, and with a cursor that already holds entries
     (append), the delta equals the oracle's and the cursor ends at the exact
     total."""
     waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
-    slots = {"small": 120, "below": 32 * waves - 1, "exact": 32 * waves,
-             "partial": 32 * waves + 1000}[case]
+    slots = {"small": 120, "below": 48 * waves - 1, "exact": 48 * waves,
+             "partial": 48 * waves + 1000}[case]
     say("case: dynamic tail", case, slots, ragged)
     n = slots * 256 - (256 - ragged if ragged else 0)
     rng = np.random.default_rng(slots)

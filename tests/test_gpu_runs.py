@@ -36,16 +36,16 @@ def cuts(kind, n, rng):
     # element long, in the partial slot at the end
     slots = (n + 255) // 256
     t, chunk = (slots - slots // 16) * 256, 96 * 256
-    return [0, n // 2 | 1, t - 300, t + 1000, t + chunk, t + 5 * chunk + 13, t + 5 * chunk + 14,
+    return [0, n // 3 | 1, 2 * (n // 3), t - 300, t + 1000, t + chunk, t + 5 * chunk + 13, t + 5 * chunk + 14,
             t + 9 * chunk + 256 * 40, n - 20, n]
 
 
 def size(kind):
     if kind == "split":
         return 5001 + (1 << 24) + 333 + 700 + 901
-    # the tail begins when the waves (12 per CU) have 32 slots each
+    # the tail begins when the waves (12 per CU) have 48 slots each
     waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
-    return (32 * waves + 1000) * 256 + 77
+    return (48 * waves + 1000) * 256 + 77
 
 
 def state(n, seed):
