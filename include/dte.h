@@ -130,7 +130,7 @@ dte_status dte_derive_scalars(const dte_adamw_step* hp, dte_scalars* out);
  *           synchronisation, *cursor > capacity means the delta is
  *           incomplete and must be recomputed with capacity >= *cursor.
  *           While the call runs, its bits from 36 up count the work units
- *           that blocks take (cleared by the call's last kernel).
+ *           that blocks take (cleared by the last block to find none left).
  * out_prev: device binary32[n] receiving theta_hat, or NULL (no write).
  * Entry order is unspecified (the set of entries is exact; each wave of the
  * kernel writes its entries in ascending runs); offsets are unique within

@@ -4,10 +4,11 @@
 // (libceilings.so), outside the C ABI of include/dte.h.
 //
 //  - ceil_read3: a plain read of three binary32 arrays (the 12 bytes per
-//    element that delta extraction must read), in extract's access pattern
-//    (persistent grid, each wave a contiguous range of 2048-element tiles,
-//    eight 16-byte non-temporal loads per lane and array in flight) with no
-//    arithmetic beyond folding the loaded bits, and no stores;
+//    element that delta extraction must read), in the pattern that measured
+//    fastest for it (persistent grid, each wave a contiguous range of
+//    2048-element tiles, eight 16-byte non-temporal loads per lane and array
+//    in flight; extraction itself keeps two in flight) with no arithmetic
+//    beyond folding the loaded bits, and no stores;
 //    ceil_read3_dynamic: the same read by one 12-wave block per CU taking
 //    four tiles per wave at a time from a counter (the CUs do not stream at
 //    one rate, so a static split ends unevenly);

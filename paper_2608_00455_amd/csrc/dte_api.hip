@@ -321,8 +321,8 @@ dte::StepScalars step_scalars(const AllScalars& sc)
     k.rbc2 = sc.s.rbc2;
     k.eps = sc.s.eps;
     k.decay = sc.s.decay;
-    // one binary32 step below and above the binary64 reciprocal: a
-    // bracket of 1/decay whatever the binary64 rounding did
+    // one binary32 step from the rounded reciprocal, away from 1: a bound
+    // of 1/decay on that side whatever the roundings did
     const float r = (float)(1.0 / (double)sc.s.decay);
     const bool grows = sc.s.decay < 1.0f;     // 1/decay > 1
     k.rd = std::nextafter(r, grows ? INFINITY : 0.0f);

@@ -75,12 +75,19 @@ struct StepScalars {
 // holds elements [end[k-1], end[k]) of the range (end[-1] = 0, end[nruns-1]
 // = n).  (The table travels as a kernel argument: 4 KB hold about 50 runs.)
 constexpr int kRunsPerLaunch = 32;
-// A run of as many elements has a launch of its own, shorter ones share: a
-// launch costs 4 to 7 us, the kernel over runs is 2 % slower than the one for
-// a single run on dense deltas, and a launch over much of the shard spreads
-// its delta over it, which apply is slower on.  Whole steps, us, every run by
-// itself -> by this rule: 13 runs of 44 M elements 260 -> 205, 16 runs of 772
-// M (42 and 151 M with vectors between them, 14 % change) 3040 -> 2918.
+// A run of as many elements has a launch of its own, shorter ones share.  A
+// launch of its own costs a run 4 to 7 us and the uneven end of its blocks;
+// sharing costs the kernel over runs, which is up to 2 % slower than the one
+// for a single run, and over most of a large sparse delta spreads the entries
+// that remap takes together over the shard.  Steps (extract, remap and apply)
+// of models with norms in a group of their own, us, at limits of 2^20 / 2^23 /
+// 2^24 / 2^26 / none: runs of up to 2.4 M elements, 27 M in all, lr 1e-5 278 /
+// 118 / 117 / 117 / 118; up to 9.4 M, 101 M in all 440 / 396 / 275 / 283 / 283,
+// lr 1e-4 553 / 497 / 420 / 418 / 418; up to 38 M, 289 M in all 877 / 870 / 833
+// / 810 / 801, 1249 / 1250 / 1209 / 1184 / 1188; up to 151 M, 1510 M in all
+// 4095 / 4085 / 4104 / 4031 / 4202, 5988 / 5977 / 5981 / 5935 / 5916.  So the
+// limit has to let runs of 10 M share and is best below the largest matrices;
+// 2^26 would be 1 to 3 % better still where runs of 17 to 67 M occur.
 constexpr int64_t kRunElements = (int64_t)1 << 24;
 struct RunTable {
     int64_t end[kRunsPerLaunch];

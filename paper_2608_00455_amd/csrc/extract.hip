@@ -5,14 +5,15 @@
 //
 // Design (HBM-bound: 12 bytes read per element, ~10 bytes written per
 // changed element):
-//  - persistent grid of one block of 12 waves per CU (three per SIMD, the
-//    VGPR limit; the block holds the CU's whole LDS); each wave owns one
-//    contiguous range of 256-element slots (one float4 per lane), ranges
-//    ascending with the global wave number, so every wave's entries leave in
-//    ascending order; in the unordered call the static ranges leave out the
-//    last 1/16 of the slots, which blocks then take eight slots per wave at a
-//    time from a counter (the CUs do not stream at one rate, and a static
-//    split leaves the fast ones idle at the end);
+//  - persistent grid of one block of 12 waves per CU (three per SIMD: the
+//    block's queues and staging areas take the CU's whole LDS; the 47 to 124
+//    VGPRs would allow four and more); each wave owns one contiguous range of
+//    256-element slots (one float4 per lane), ranges ascending with the global
+//    wave number, so every wave's entries leave in ascending order; in the
+//    unordered call over 48 slots per wave and more the static ranges leave
+//    out the last 1/16 of the slots, which blocks then take eight slots per
+//    wave at a time from a counter (the CUs do not stream at one rate, and a
+//    static split leaves the fast ones idle at the end);
 //    a wave keeps two slots of p, m and v in flight, reloading each slot's
 //    registers as soon as it is tested;
 //  - proof of "unchanged" before exact arithmetic: with DECAY == 1 the
@@ -34,10 +35,10 @@
 //    candidates are queued, and changed entries (32-bit position +
 //    BF16 value) staged in LDS, in ascending element order: every wave's
 //    output is ascending.  In the unordered call the waves of a block meet
-//    every one to four passes over the ring and, once they hold enough entries, reserve output
-//    space for all of them with one atomicAdd on the 64-bit cursor
-//    (block_round below); each wave writes its run after those of the waves
-//    before it, coalesced.  A wave whose staging area (kWaveStage entries)
+//    every one to four passes over the ring and, once they hold enough
+//    entries, reserve output space for all of them with one atomicAdd on the
+//    64-bit cursor (block_round below); each wave writes its run after those
+//    of the waves before it, coalesced.  A wave whose staging area (kWaveStage entries)
 //    fills between two meetings flushes exactly kWaveStage entries on its
 //    own with one atomicAdd;
 //  - ordered mode: the waves of a block still meet every four passes (a
@@ -195,8 +196,8 @@ constexpr int64_t kDenseRatio = 64;             // see write_staged
 
 // Dynamic tail of the unordered call: when the waves have at least
 // kTailSlots slots each, the last total / kTailDiv slots (at most 2^23, so
-// that an element's offset from the tail's start fits a staging key) go to
-// blocks kRound passes per wave per grab.  A grab adds
+// that an element's offset from the tail's start fits a staging key; the
+// partial slot among them) go to blocks kRound passes per wave per grab.  A grab adds
 // 2^kGrabShift to the caller's cursor, whose bits below kGrabShift count the
 // entries (a delta never reaches 2^36 entries): the old value's high bits
 // number the chunk, every reservation masks them off, and the block whose
@@ -434,10 +435,10 @@ __device__ __forceinline__ void stage_changed(const ExtractParams& a, const Wave
 }
 
 // Combined flushes of the unordered call.  Every kRound passes over the ring
-// (fewer in dense ranges), and once at the end, the waves of a block meet at a barrier; when they hold at
-// least kFlushPerWave entries per wave (at the end: any), one atomicAdd on the
-// cursor reserves room for all of them and each wave writes its entries
-// after those of the waves before it.  Every wave of the device reserving
+// (fewer in dense ranges), and once at the end, the waves of a block meet at a
+// barrier; when they hold at least kFlushPerWave entries per wave (at the end:
+// any), one atomicAdd on the cursor reserves room for all of them and each
+// wave writes its entries after those of the waves before it.  Every wave of the device reserving
 // its own space from the one cursor address is what slows the stream (the
 // atomics, not the stores), so fewer, larger reservations are the point; a
 // wave whose staging area fills between two meetings still flushes on its
@@ -445,6 +446,10 @@ __device__ __forceinline__ void stage_changed(const ExtractParams& a, const Wave
 // is rewritten only after every wave has passed a later barrier.
 constexpr int kRound = 4;
 constexpr int kFlushPerWave = 768;            // block flush threshold per wave
+// Entries that a wave finds between two meetings: those of kRound passes, of
+// candidates left in the queue before them and of the range's partial slot.
+constexpr int kMaxFound = kRound * kVec * kSlot + kDrain - 1 + kSlot;
+static_assert(kMaxFound < 1 << 15 && kWaveStage < 1 << 16, "block_round packs both in one int");
 
 // Returns the number of passes until the next meeting: as many (up to
 // kRound) as leave room for what the block's waves found per pass since the
@@ -454,7 +459,6 @@ __device__ int block_round(const ExtractParams& a, const WaveStage& st, Staging&
                            int wave, int (*s_cnt)[kWaves], unsigned long long* s_base, int slot,
                            int passes, bool last_round)
 {
-    // (at most kRound * kVec * kSlot entries found: 16 bits each)
     const int64_t all = so.flushed + so.staged;
     if (lane == 0) s_cnt[slot][wave] = so.staged | ((int)(all - so.met) << 16);
     so.met = all;
@@ -517,9 +521,9 @@ __device__ void drain_queue(const ExtractParams& a, const StepScalars& k, const 
 __device__ const f32x4 g_pad = {};
 
 // The float4 of each lane in the whole slot at element e0 of the range, or
-// (one request for the wave) the pad: loads are issued on every path, so that the number of loads in
-// flight behind a slot's own is known where the slot is tested.  Element
-// alignment is enough for 16-byte global loads.
+// (one request for the wave) the pad: loads are issued on every path, so that
+// the number of loads in flight behind a slot's own is known where the slot is
+// tested.  Element alignment is enough for 16-byte global loads.
 __device__ __forceinline__ void load_slot(const ExtractParams& a, bool valid, int64_t e0, int lane,
                                           f32x4& P, f32x4& M, f32x4& V)
 {
@@ -899,7 +903,8 @@ void launch_kernel(const ExtractParams& a, dim3 grid, hipStream_t s)
         hipLaunchKernelGGL((extract_kernel<F, true, D, false, L, false>), grid, block, 0, s, a);
 }
 
-// Blocks of one call: a slot per wave at least, one block per CU at most.
+// Blocks of one call: as many as get kMinSlots slots per wave, rounded up
+// (the last block may get fewer), one per CU at most.
 int64_t blocks_of(int64_t n, int cus)
 {
     const int64_t slots = (n + kSlot - 1) / kSlot;

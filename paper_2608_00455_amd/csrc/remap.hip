@@ -240,10 +240,13 @@ constexpr int kApplyUnroll = 8;
 // per CU and 1 to 8 chains per lane measured within 3 % of each other).  The
 // stores go past the caches: kept in L2, the dirty lines of a shard that
 // nobody reads until the next delta are written back in the next kernels'
-// time.  Whole steps on shards that are not cached, ordinary -> non-temporal
-// stores for sparse deltas, us: four Qwen3-8B layers, TP=4, lr 1e-6 1508 ->
-// 1484; sixteen layers, TP=8 6396 -> 6302; Qwen3-30B-A3B layers, EP=8, lr
-// 1e-5 2788 -> 2720; 2 and 11 M elements unchanged.
+// time.  On shards that are not cached, ordinary -> non-temporal stores, us of
+// the kernel and of it with what it leaves to the next one: 0.1 M entries (11
+// M elements) 8.5 / 11 -> 8.2 / 3.5; 0.3 M (four Qwen3-8B layers, lr 1e-7) 20.5
+// / 41 -> 20 / 16; 2.4 M (lr 1e-6) 110 / 135 -> 113 / 109; 17.5 M (lr 1e-5) 520
+// / 550 -> 474 / 454.  (Only the same entries applied again to lines that the
+// last-level cache still holds are faster with ordinary stores: 50 against 106
+// us for 2.4 M.)
 __global__ __launch_bounds__(kBlock) void apply_kernel(ApplySlice s,
                                                       const int64_t* __restrict__ rank_count)
 {

@@ -152,8 +152,8 @@ __device__ __forceinline__ void unravel(uint32_t li, int nd, const uint32_t* sha
 // chunk spans several segments).  Counters: lane r of `runv` holds the
 // running count of rank first + r, lane r of `basev` the reserved bucket
 // start.  kWrite == false counts outputs; kWrite == true writes them.
-// kShapeRegs: unravel over the shape cached in `cache` (else re-read it,
-// which needs fewer registers).
+// kShapeRegs: unravel over the shape cached in `cache` (else re-read it: the
+// caller keeps four scalar registers fewer).
 template <bool kWrite, bool kShapeRegs = true>
 __device__ __forceinline__ void route_slot(const PlanView& pl, const RankSlice& out, int lane,
                                            int64_t i, uint16_t v, int& runv, int64_t basev,
