@@ -2,10 +2,13 @@
 """Throughput of the delta-extraction hot path on one MI355X.
 
 One step = one pass of the whole path over the trainer shard already
-resident in HBM: reset the delta cursor, dte_extract_delta (AdamW
-inversion + BF16 change detection + compaction; --ordered:
-dte_extract_delta_ordered, an ascending delta), dte_remap (receiver
-coordinates) and dte_apply (scatter into the receiver BF16 shards).
+resident in HBM, DeltaPipeline.step: clear the cursor and the rank counts,
+dte_extract_delta (AdamW inversion + BF16 change detection + compaction;
+--ordered: dte_extract_delta_ordered, an ascending delta; dte_extract_runs
+over several parameter groups), then dte_remap_apply (receiver coordinates
+and scatter into the receiver BF16 shards).  The single calls
+(dte_extract_delta, dte_remap, dte_apply) are timed in as many passes of
+their own after the steps.
 
 Default workload: the full Qwen3-8B state (8,190,735,360 fp32 elements of
 theta, m, v; receiver TP=4).  Prints one JSON line with the throughput in
@@ -99,10 +102,9 @@ def measured_traffic(workload_name, kernel, mode):
 
 def ceilings(p, m, v, pipe, stream, entries, reps=5, touch=None):
     """Second denominators measured on the same GPU and buffers: the rate of
-    a plain read of theta, m, v (12 bytes per element, extract's access
-    pattern, no arithmetic, no stores; best of 2, 3 and 4 blocks per CU
-    with a static split and of one 12-wave block per CU taking four tiles
-    per wave at a time);
+    a plain read of theta, m, v (12 bytes per element, no arithmetic, no
+    stores; best of 2, 3 and 4 blocks per CU with a static split and of one
+    12-wave block per CU taking four tiles per wave at a time);
     the writes of an `entries`-entry delta alone (8-byte offsets and 2-byte
     values spread evenly over the tiles, into the pipeline's delta buffers,
     which the step has finished with; same block counts), whose time added
@@ -370,29 +372,30 @@ def main():
     flush = (torch.zeros(int(flush_gb * 1e9) // 8, dtype=torch.float32, device="cuda")
              if flush_gb > 0 else None)
 
-    # events per step: 0 step start (before the cursor reset), 1 extract
-    # start, 2 extract end, 3 remap end, 4 apply end
-    def step(ev=None):
-        rec = (lambda i: ev[i].record(stream)) if ev else (lambda i: None)
-        rec(0)
+    def step():
         if apply_only:
-            rec(1)
-            rec(2)
-            rec(3)
             pipe.apply()
-            rec(4)
-            return
+        else:
+            pipe.step(p, m, v, hp, runs=runs if len(runs) > 1 else None)
+
+    # the single calls; events: 0 extract start (after the cursor reset), 1
+    # extract end, 2 remap end, 3 apply end
+    def calls(ev):
         pipe.reset()
-        rec(1)
+        ev[0].record(stream)
         if len(runs) == 1:
             pipe.extract(p, m, v, hp)
         else:
             pipe.extract_runs(p, m, v, runs)
-        rec(2)
+        ev[1].record(stream)
         pipe.remap()
-        rec(3)
+        ev[2].record(stream)
         pipe.apply()
-        rec(4)
+        ev[3].record(stream)
+
+    def events(n):
+        return [[torch.cuda.Event(enable_timing=True) for _ in range(n)]
+                for _ in range(args.steps)]
 
     if apply_only:                           # delta and buckets prepared untimed
         pipe.step(p, m, v, hp)
@@ -401,7 +404,7 @@ def main():
             flush.add_(1.0)
         step()
     torch.cuda.synchronize()
-    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(5)] for _ in range(args.steps)]
+    evs = events(2)
     start = torch.cuda.Event(enable_timing=True)
     end = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -409,11 +412,13 @@ def main():
     for k in range(args.steps):
         if flush is not None:
             flush.add_(1.0)                  # reads and writes flush_gb GB, outside the step
-        step(evs[k])
+        evs[k][0].record(stream)
+        step()
+        evs[k][1].record(stream)
     end.record(stream)
     torch.cuda.synchronize()
     total_ms = start.elapsed_time(end)
-    per_step = [e[0].elapsed_time(e[4]) for e in evs]
+    per_step = [e[0].elapsed_time(e[1]) for e in evs]
     # with a cache flush between steps the step time is the steps' own
     # events; else the whole bracketed interval
     ms_step = sum(per_step) / args.steps if flush is not None else total_ms / args.steps
@@ -424,17 +429,21 @@ def main():
         log("bench: capacity exceeded (changed %d, capacity %d)" % (changed, cap))
         return 3
     c = changed / n
-    ext = _stats([e[1].elapsed_time(e[2]) for e in evs])
-    rem = _stats([e[2].elapsed_time(e[3]) for e in evs])
-    app = _stats([e[3].elapsed_time(e[4]) for e in evs])
-
     if apply_only:
-        k = app
+        ext = rem = None
+        k = app = _stats(per_step)
         k_bytes = routed * (8 + 2 + 2)       # read offset + value, write value
         value = routed / (ms_step / 1e3)
         metric_unit = "entries/s"
         kernel = "apply"
     else:
+        evs = events(4)
+        for e in evs:
+            if flush is not None:
+                flush.add_(1.0)
+            calls(e)
+        torch.cuda.synchronize()
+        ext, rem, app = (_stats([e[i].elapsed_time(e[i + 1]) for e in evs]) for i in range(3))
         k = ext
         k_bytes = 12 * n + 10 * changed       # read theta, m, v; write (idx, val)
         value = n / (ms_step / 1e3)
@@ -443,7 +452,8 @@ def main():
     if apply_only:
         step_bytes = k_bytes
     else:
-        step_bytes = 12 * n + 10 * changed + 10 * changed + 10 * routed + 12 * routed
+        # read the state, write and read the delta, write buckets and values
+        step_bytes = 12 * n + 20 * changed + 12 * routed
     achieved = k_bytes / (k["mean"] / 1e3) / 1e9
     # the counters were taken for the default configuration only (folded
     # order, unordered output, one parameter group)
