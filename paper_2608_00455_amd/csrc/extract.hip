@@ -11,7 +11,7 @@
 //    256-element slots (one float4 per lane), ranges ascending with the global
 //    wave number, so every wave's entries leave in ascending order; in the
 //    unordered call over 48 slots per wave and more the static ranges leave
-//    out the last 1/16 of the slots, which blocks then take eight slots per
+//    out the last 1/16 of the slots, which blocks then take 8 or 32 slots per
 //    wave at a time from a counter (the CUs do not stream at one rate, and a
 //    static split leaves the fast ones idle at the end);
 //    a wave keeps two slots of p, m and v in flight, reloading each slot's
@@ -197,7 +197,7 @@ constexpr int64_t kDenseRatio = 64;             // see write_staged
 // Dynamic tail of the unordered call: when the waves have at least
 // kTailSlots slots each, the last total / kTailDiv slots (at most 2^23, so
 // that an element's offset from the tail's start fits a staging key; the
-// partial slot among them) go to blocks kRound passes per wave per grab.  A grab adds
+// partial slot among them) go to blocks chunk_slots per wave per grab.  A grab adds
 // 2^kGrabShift to the caller's cursor, whose bits below kGrabShift count the
 // entries (a delta never reaches 2^36 entries): the old value's high bits
 // number the chunk, every reservation masks them off, and the block whose
@@ -213,6 +213,17 @@ constexpr int64_t kDenseRatio = 64;             // see write_staged
 constexpr int64_t kTailDiv = 16;
 constexpr int64_t kTailSlots = 48;
 constexpr int64_t kMaxTailSlots = (int64_t)1 << 23;
+// Slots per wave of one grab: few (one meeting's passes) let the blocks end
+// together, but a wave's entries from the tail are then short pieces far
+// apart, and where a delta is sparse and the plan has many segments remap
+// routes them lane by lane.  With 8 / 16 / 32 / 64: extract of 38 M elements
+// 74.5 / 78.1 / 87.9 / 110.8 us, of 320 M 562 / 564 / 568 / 576, of 772 M 1328
+// / 1327 / 1329 / 1339; remap of twelve Qwen3-30B-A3B layers' delta (7477 M
+// elements, 0.087 % change) 314 / 196 / 140 / 139, their extract 13430 / 13424
+// / 13364 / 13337, of sixteen Qwen3-8B layers' (3104 M) 201 / 198 / 189 / 174.
+// So the longer grabs from four of them per block on (1611 M elements).
+constexpr int64_t kChunkSlots = 8, kLongChunkSlots = 32;
+constexpr int64_t kLongChunks = 4;
 constexpr int kGrabShift = 36;
 constexpr unsigned long long kCountMask = (1ull << kGrabShift) - 1;
 
@@ -220,6 +231,11 @@ __device__ inline int64_t tail_slots(int64_t slots, int64_t waves)
 {
     const int64_t d = slots >= kTailSlots * waves ? slots / kTailDiv : 0;
     return d < kMaxTailSlots ? d : kMaxTailSlots;
+}
+
+__device__ inline int64_t chunk_slots(int64_t tail, int64_t waves)
+{
+    return tail >= kLongChunks * kLongChunkSlots * waves ? kLongChunkSlots : kChunkSlots;
 }
 
 // Per-wave LDS areas.  Keys are element offsets from element `base` of the
@@ -788,25 +804,25 @@ __global__ __launch_bounds__(64 * kWaves) void extract_kernel(ExtractParams a)
             st.base = s_last * kSlot;
             in_tail = true;
         }
-        constexpr int64_t kWaveChunk = kRound * kVec, kChunk = kWaves * kWaveChunk;
+        const int64_t wave_chunk = chunk_slots(tail, nw), block_chunk = kWaves * wave_chunk;
         if (threadIdx.x == 0)
             s_chunk = atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
                                 1ull << kGrabShift) >> kGrabShift;
         __syncthreads();
         const int64_t chunk = rt::readlane64((int64_t)s_chunk, 0);   // block-uniform
         __syncthreads();                                     // s_chunk is rewritten next
-        if (chunk * kChunk >= tail) {
+        if (chunk * block_chunk >= tail) {
             // chunks and one empty grab per block: the last of them clears
             // the grab count
-            const int64_t grabs = (tail + kChunk - 1) / kChunk + gridDim.x;
+            const int64_t grabs = (tail + block_chunk - 1) / block_chunk + gridDim.x;
             if (threadIdx.x == 0 && chunk == grabs - 1)
                 atomicAdd(reinterpret_cast<unsigned long long*>(a.cursor),
                           0ull - ((unsigned long long)grabs << kGrabShift));
             break;
         }
-        first = s_last + chunk * kChunk + wave * kWaveChunk;
-        last = first + kWaveChunk < slots ? first + kWaveChunk : slots;
-        iters = kRound;
+        first = s_last + chunk * block_chunk + wave * wave_chunk;
+        last = first + wave_chunk < slots ? first + wave_chunk : slots;
+        iters = wave_chunk / kVec;
         it = -1;
     }
     if (queued > 0) drain_queue<kDecayOne, kLit, kRoute>(a, step, st, queued, queued, so, lane);

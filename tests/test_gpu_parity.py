@@ -744,3 +744,54 @@ def test_unordered_tail_taken_in_chunks(case, ragged):
         order = np.argsort(got_i)
         assert np.array_equal(got_i[order], np.concatenate([want_idx, want_idx + n]))
         assert np.array_equal(got_v[order], np.concatenate([want_val, want_val]))
+
+
+@pytest.mark.parametrize("more", [-1, 0, 1000])
+def test_large_tail_in_few_pieces(more):
+    """From 2048 slots per wave on the dynamic tail is taken 32 slots per wave
+    at a time: the delta equals the ordered call's at, below and above that
+    size, and falls into few pieces (remap takes 512 entries together, and is
+    fast where these lie in one segment)."""
+    waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+    slots = 2048 * waves + more
+    n = slots * 256
+    say("case: large tail", slots)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    p, m, v = (torch.empty(n, dtype=torch.float32, device="cuda").normal_(0.0, sd, generator=gen)
+               for sd in (0.02, 1e-4, 1e-6))
+    v.abs_()
+    hp = W.StepHP(lr=1e-6)
+    cap = n // 50
+    s = torch.cuda.current_stream().cuda_stream
+    got = []
+    for ordered in (False, True):
+        idx = torch.empty(cap, dtype=torch.int64, device="cuda")
+        val = torch.empty(cap, dtype=torch.int16, device="cuda")
+        cursor = torch.zeros(1, dtype=torch.int64, device="cuda")
+        args = (p.data_ptr(), m.data_ptr(), v.data_ptr(), n, 0, hp, idx.data_ptr(),
+                val.data_ptr(), cap, cursor.data_ptr())
+        if ordered:
+            ws = torch.empty(B.dte_ordered_workspace_bytes(cap), dtype=torch.uint8, device="cuda")
+            B.dte_extract_delta_ordered(*args, ws.data_ptr(), ws.numel(), 0, s)
+        else:
+            B.dte_extract_delta(*args, 0, s)
+        sync()
+        k = int(cursor.item())
+        assert 0 < k <= cap
+        got.append((idx[:k], val[:k]))
+    (ui, uv), (oi, ov) = got
+    srt, order = torch.sort(ui)
+    assert torch.equal(srt, oi) and torch.equal(uv[order], ov)
+    # pieces: neighbours of the delta that lie more than half a small block
+    # chunk apart.  Each grab gives a wave one piece, each of its write-outs
+    # another (768 entries on average, but for its last ones and those at the
+    # switch to the tail).
+    far = (ui[1:] - ui[:-1]).abs() > 12 * 8 * 256 // 2
+    pieces = int(far.sum().item()) + 1
+    tail, short, long = slots // 16, 8, 32
+    rest = ui.numel() // 512 + 6 * waves
+    assert tail // short > tail // long + rest        # the bound tells the two sizes apart
+    if more < 0:
+        assert tail // short * 0.9 < pieces <= tail // short + rest, pieces
+    else:
+        assert pieces <= tail // long + rest, pieces
