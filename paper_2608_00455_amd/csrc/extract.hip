@@ -218,12 +218,16 @@ constexpr int64_t kMaxTailSlots = (int64_t)1 << 23;
 // apart, and where a delta is sparse and the plan has many segments remap
 // routes them lane by lane.  With 8 / 16 / 32 / 64: extract of 38 M elements
 // 74.5 / 78.1 / 87.9 / 110.8 us, of 320 M 562 / 564 / 568 / 576, of 772 M 1328
-// / 1327 / 1329 / 1339; remap of twelve Qwen3-30B-A3B layers' delta (7477 M
-// elements, 0.087 % change) 314 / 196 / 140 / 139, their extract 13430 / 13424
-// / 13364 / 13337, of sixteen Qwen3-8B layers' (3104 M) 201 / 198 / 189 / 174.
-// So the longer grabs from four of them per block on (1611 M elements).
+// / 1327 / 1329 / 1339; remap of 787 M elements in ten layers of 64 experts, lr 1e-6
+// 78 / 65 / 63 / -, of twelve Qwen3-30B-A3B layers (7477 M, 0.087 % change) 314
+// / 196 / 140 / 139, their extract 13430 / 13424 / 13364 / 13337, remap of
+// sixteen Qwen3-8B layers (3104 M) 201 / 198 / 189 / 174.  In between both show:
+// 289 M elements extract 525 / 527 / 526 and remap 62 / 60 / 44 in six equal
+// layers, 512 / 515 / 516 and 39 / 40 / 42 in three layers of another layout.
+// So the longer grabs where the tail has kLongTail slots per wave (604 M
+// elements in all), where they cost extract nothing.
 constexpr int64_t kChunkSlots = 8, kLongChunkSlots = 32;
-constexpr int64_t kLongChunks = 4;
+constexpr int64_t kLongTail = 48;
 constexpr int kGrabShift = 36;
 constexpr unsigned long long kCountMask = (1ull << kGrabShift) - 1;
 
@@ -235,7 +239,7 @@ __device__ inline int64_t tail_slots(int64_t slots, int64_t waves)
 
 __device__ inline int64_t chunk_slots(int64_t tail, int64_t waves)
 {
-    return tail >= kLongChunks * kLongChunkSlots * waves ? kLongChunkSlots : kChunkSlots;
+    return tail >= kLongTail * waves ? kLongChunkSlots : kChunkSlots;
 }
 
 // Per-wave LDS areas.  Keys are element offsets from element `base` of the

@@ -748,12 +748,12 @@ def test_unordered_tail_taken_in_chunks(case, ragged):
 
 @pytest.mark.parametrize("more", [-1, 0, 1000])
 def test_large_tail_in_few_pieces(more):
-    """From 2048 slots per wave on the dynamic tail is taken 32 slots per wave
+    """From 768 slots per wave on the dynamic tail is taken 32 slots per wave
     at a time: the delta equals the ordered call's at, below and above that
     size, and falls into few pieces (remap takes 512 entries together, and is
     fast where these lie in one segment)."""
     waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
-    slots = 2048 * waves + more
+    slots = 768 * waves + more
     n = slots * 256
     say("case: large tail", slots)
     gen = torch.Generator(device="cuda").manual_seed(7)
@@ -784,12 +784,12 @@ def test_large_tail_in_few_pieces(more):
     assert torch.equal(srt, oi) and torch.equal(uv[order], ov)
     # pieces: neighbours of the delta that lie more than half a small block
     # chunk apart.  Each grab gives a wave one piece, each of its write-outs
-    # another (768 entries on average, but for its last ones and those at the
+    # another (768 entries on average, but for its last one and that at the
     # switch to the tail).
     far = (ui[1:] - ui[:-1]).abs() > 12 * 8 * 256 // 2
     pieces = int(far.sum().item()) + 1
     tail, short, long = slots // 16, 8, 32
-    rest = ui.numel() // 512 + 6 * waves
+    rest = ui.numel() // 768 + 3 * waves
     assert tail // short > tail // long + rest        # the bound tells the two sizes apart
     if more < 0:
         assert tail // short * 0.9 < pieces <= tail // short + rest, pieces
