@@ -193,7 +193,10 @@ class DeltaPipeline:
                             self.rank_count.data_ptr(), self.cursor.data_ptr(), _stream(stream))
 
     def step_fused(self, p, m, v, hp, stream=None, runs=None):
-        """The step with detection, remap and apply in one kernel."""
+        """The step with detection, remap and apply in one kernel: the delta
+        arrays stay unwritten.  step is faster at most sizes (four Qwen3-8B
+        layers 1.4 against 1.5 ms at lr 1e-6, 3.0 against 3.6 at 1e-4); this
+        one is on 25 to 300 M elements at a few percent change."""
         self._reset_counters(stream)
         runs = list(runs) if runs is not None else None
         if runs is None:
@@ -210,7 +213,8 @@ class DeltaPipeline:
 
     def step(self, p, m, v, hp, stream=None, runs=None):
         """Fresh counters, extract (over `runs` when the shard has several
-        parameter groups), remap and apply."""
+        parameter groups), remap and apply.  (A call that is refused leaves
+        the counters cleared.)"""
         self._reset_counters(stream)
         if runs is None:
             self.extract(p, m, v, hp, stream=stream)
